@@ -10,6 +10,7 @@
 // from the definition in include/dat.h.
 #include "common.h"
 #include "philox.h"
+#include "tensor_table.h"
 
 namespace dat {
 namespace {
@@ -17,26 +18,6 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kIter = 8;          // groups per thread
 constexpr uint32_t kStreamQuant = 0;
-
-__device__ __forceinline__ int find_tensor(const int64_t* off, int T, int64_t i) {
-  // largest t with off[t] <= i  (off[0] = 0, off[T] = d > i); empty tensors are skipped
-  int lo = 0, hi = T;
-  while (hi - lo > 1) {
-    int mid = (lo + hi) >> 1;
-    if (off[mid] <= i) lo = mid; else hi = mid;
-  }
-  return lo;
-}
-
-// The offset table in LDS (T <= kTabMax): the binary search and every tensor boundary a thread crosses then
-// cost LDS reads instead of dependent global loads.  Returns the table to use (generic pointer).
-constexpr int kTabMax = 1024;
-__device__ __forceinline__ const int64_t* stage_offsets(const int64_t* __restrict__ off, int T, int64_t* s_off) {
-  if (T > kTabMax) return off;
-  for (int i = threadIdx.x; i <= T; i += blockDim.x) s_off[i] = off[i];
-  __syncthreads();
-  return s_off;
-}
 
 __global__ void fill_u32_kernel(uint32_t* p, int n, uint32_t v) {
   int i = blockIdx.x * blockDim.x + threadIdx.x;

@@ -59,3 +59,25 @@ def test_lamb_update_matches_reference(dat, use_adam):
             err = np.abs(got[lo:hi] - ref_theta[lo:hi]).max()
             assert err <= 2e-6 * max(np.abs(ref_theta[lo:hi]).max(), 1e-3), (step, t, err)
     model.close()
+
+
+@pytest.mark.parametrize("bits,M", [(2, 5), (4, 4), (8, 1), (8, 7), (8, 8), (16, 9)])
+def test_aggregate_long_tensors(dat, bits, M):
+    """Tensors longer than a workgroup's span (the path with one scale per worker), borders inside a span, groups of
+    workers that are not full, a ragged end."""
+    off = np.array([0, 70001, 70002, 70010, 140000, 151111], np.int64)
+    d, S = int(off[-1]), oracle.levels(bits)
+    rng = np.random.default_rng(bits * 100 + M)
+    od = _cuda(off)
+    qs, scs, cs, ss = [], [], [], []
+    for i in range(M):
+        g = rng.standard_normal(d).astype(np.float32) * np.float32(10.0 ** (i % 3 - 2))
+        c, s = oracle.quantize(g, off, S, 70 + i)
+        q, sc = dat.quantize(_cuda(g), od, bits, 70 + i)
+        qs.append(q); scs.append(sc); cs.append(c); ss.append(s)
+    want = oracle.aggregate(cs, ss, off, S)
+    assert np.array_equal(dat.aggregate(qs, scs, od, d, bits).cpu().numpy(), want)
+    guard = torch.full((d + 8,), 7.0, device="cuda")     # an output that is aligned to one float only; nothing beyond it is written
+    dat.aggregate(qs, scs, od, d, bits, out=guard[1:d + 1])
+    got = guard.cpu().numpy()
+    assert np.array_equal(got[1:d + 1], want) and (got[d + 1:] == 7.0).all() and got[0] == 7.0
