@@ -42,7 +42,9 @@ struct ConvGeom {
 // ---- fp32 direct convolutions (conv_direct.hip): the DAT_F32 path ------------------------------
 dat_status conv_direct_forward(const float* x, const float* w, const float* res, float* y, const ConvGeom& g, hipStream_t st);
 dat_status conv_direct_backward_data(const float* dy, const float* w, float* dx, const ConvGeom& g, bool accumulate, hipStream_t st);
-dat_status conv_direct_backward_weight(const float* x, const float* dy, float* dw, const ConvGeom& g, float scale, hipStream_t st);
+// ws: conv_direct_wgrad_workspace(g) bytes (fp64 partial sums over pixel ranges); never smaller for a larger batch
+size_t conv_direct_wgrad_workspace(const ConvGeom& g);
+dat_status conv_direct_backward_weight(const float* x, const float* dy, float* dw, const ConvGeom& g, float scale, void* ws, hipStream_t st);
 
 // ---- bf16 implicit-GEMM convolutions on MFMA (conv_mfma.hip): the DAT_BF16 path ----------------
 // w: [Cout][k][k][Cin] bf16.  wT: the backward-data operand built by launch_weight_transform

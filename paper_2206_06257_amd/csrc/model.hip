@@ -465,6 +465,8 @@ dat_status allocate(dat_model& m) {
   if (ws) DAT_TRY(dev_alloc(m, &m.wgrad_ws, ws));
   size_t partial_floats = bn_partial_floats(0, cmax);
   for (const Op& op : m.ops) {
+    // fp32 models: the partial sums of a backward-weight pass share the buffer (they live inside one launch pair)
+    if (op.kind == OP_CONV && m.dtype == DAT_F32) partial_floats = std::max(partial_floats, conv_direct_wgrad_workspace(geom_of(m, op, m.maxB)) / 4);
     if (op.kind != OP_CONV || m.dtype != DAT_BF16) continue;
     const Shape si = m.tens[op.in], so = m.tens[op.out];
     const int sf = conv_stat_slabs((int64_t)m.maxB * so.H * so.W, 1), sb = conv_stat_slabs((int64_t)m.maxB * si.H * si.W, op.stride);
@@ -633,7 +635,7 @@ dat_status backward(dat_model& m, int B, float* grads, bool need_input_grad, hip
           }
           if (dt == DAT_BF16 && op.blocked) DAT_PROF(m, DAT_PROF_CONV_WGRAD, conv_flops(g, op.cin_real), wst, conv_mfma_stem_backward_weight((const bf16_t*)m.act[op.in], (const bf16_t*)m.grad[op.out], g0, op.dv, op.cin_real, g, 1.0f, m.wgrad_ws, wst, slot(op.p0)));
           else if (dt == DAT_BF16) DAT_PROF(m, DAT_PROF_CONV_WGRAD, conv_flops(g, op.cin_real), wst, conv_mfma_backward_weight((const bf16_t*)m.act[op.in], (const bf16_t*)m.grad[op.out], g0, op.cin_real, g, 1.0f, m.wgrad_ws, wst, slot(op.p0)));
-          else DAT_PROF(m, DAT_PROF_CONV_WGRAD, conv_flops(g, op.cin_real), st, conv_direct_backward_weight((const float*)m.act[op.in], (const float*)m.grad[op.out], g0, g, 1.0f, st));
+          else DAT_PROF(m, DAT_PROF_CONV_WGRAD, conv_flops(g, op.cin_real), st, conv_direct_backward_weight((const float*)m.act[op.in], (const float*)m.grad[op.out], g0, g, 1.0f, m.partial, st));
         }
         if (op.in != 0 || need_input_grad) {
           // sums of the BN whose output gradient this pass completes (nothing else has written it, nothing else will)
