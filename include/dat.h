@@ -334,14 +334,14 @@ typedef enum { DAT_OPT_FUSE_BN_INPUT_GRAD = 0, DAT_OPT_FUSE_BN_SUMS = 1, DAT_OPT
                DAT_OPT_KEEP_BOTH_PASSES = 8 } dat_option;
 dat_status dat_model_set_option(dat_model* m, dat_option opt, int value);
 /* Process-wide kernel selection (ablations and tests; an atomic flag, read at every convolution launch of every
- * model and of the dat_conv_* entry points).  DAT_KOPT_RING_KERNEL (default 1): layers that run as one round of
- * 256-channel tiles go through the multi-stage kernel; 0: through the 128x128 kernels.  The convolution outputs
- * are bit-identical, the grouping of the batch-norm partial sums differs (256 instead of 128 pixels per slab).
- * DAT_KOPT_TILE_160 (default 1): layers with 160 or 320 output channels (the wide ResNets)
- * run in 160-channel tiles; 0: in 128-channel tiles, the last one partly empty.  Bit-identical outputs.
- * DAT_KOPT_NARROW_UNDERFILLED (default 1): a layer with a contraction >= 1024 whose 128x128 tiles would number at
- * most 1.5 per compute unit runs in 32-channel tiles; 0: in 128-channel tiles.  Bit-identical outputs (the partial
- * sums of the batch statistics are grouped differently). */
+ * model and of the dat_conv_* entry points).  With an option off its layers run in 128-channel tiles of the
+ * single-stage kernels; the convolution outputs are bit-identical, the grouping of the batch-norm partial sums differs.
+ * DAT_KOPT_RING_KERNEL (default 1): long contractions that are one round of 256-channel tiles go through the
+ * multi-stage kernel.
+ * DAT_KOPT_TILE_160 (default 1): layers whose output channels are a multiple of 160 (the wide ResNets) run in
+ * 160-channel tiles.
+ * DAT_KOPT_NARROW_UNDERFILLED (default 1): a layer whose 128x128 tiles would number at most one per compute unit runs
+ * through the multi-stage kernel, in tiles the narrower the fewer there are. */
 typedef enum { DAT_KOPT_RING_KERNEL = 0, DAT_KOPT_TILE_160 = 1, DAT_KOPT_NARROW_UNDERFILLED = 2 } dat_kernel_option;
 dat_status dat_set_kernel_option(dat_kernel_option opt, int value);
 

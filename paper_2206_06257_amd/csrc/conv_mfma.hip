@@ -9,11 +9,11 @@
 //   the NHWC input, gathered on the fly: 8 consecutive k are 8 consecutive channels of one tap,
 //   i.e. one 16-byte vector.  Both operands sit in LDS as [row][BK k] tiles (BK = 32 or 64) with
 //   an XOR swizzle of the 16-byte slots so that the 16-byte fragment reads of the 32 lanes
-//   sharing a k-slot hit distinct banks.  Two kernels fill those tiles:
+//   sharing a k-slot hit distinct banks.  Three kernels fill those tiles:
 //   * `igemm_dma_kernel` (contraction channels a multiple of BK): global memory -> LDS directly
-//     (global_load_lds_dwordx4), one LDS stage, four or more workgroups resident per CU;
-//   * `igemm_ring_kernel` (long contractions into a multiple of 256 channels that fill the chip with one
-//     round of tiles): 8 waves, 256-channel tiles, a ring of LDS stages filled by the same direct loads;
+//     (buffer_load_dwordx4 ... lds), one LDS stage, four or more workgroups resident per CU;
+//   * `igemm_ring_kernel` (layers with at most a few workgroups per CU, and the wide ResNets' multiples of 160
+//     channels): one or two workgroups per CU, a ring of LDS stages filled by the same direct loads;
 //   * `igemm_kernel` (any channel count, and the long 1x1 contractions into <= 64 channels):
 //     global -> registers -> LDS, double buffered, loads running PF k-tiles ahead.
 //   Backward-data is the same contraction over the output gradient: stride 1 with the flipped,
@@ -64,7 +64,7 @@ template <> __device__ __forceinline__ int swz<8>(int row, int slot) {
   return row * 128 + ((slot ^ f) << 4);
 }
 
-// Out-of-range and padding vectors are read from this zero page instead of being masked.
+// Out-of-range and padding vectors of igemm_kernel are read from this zero page instead of being masked.
 __device__ __attribute__((aligned(16))) uint32_t g_zero_page[4] = {0u, 0u, 0u, 0u};
 
 struct IgemmArgs {
@@ -365,6 +365,7 @@ __global__ __launch_bounds__(kThreads, OCC) void igemm_kernel(IgemmArgs a) {
   }
   const int ntiles = (a.Ktot + BKT - 1) / BKT;
   const u32x4* zero_page = reinterpret_cast<const u32x4*>(g_zero_page);
+  asm("" : "+s"(zero_page));     // (kept in registers: the compiler would load the symbol's address again in every k-tile)
 
   // Weight rows of this thread: offset of (row, k = kvec*8) and row validity; advances by BK per tile.
   int woff[VW]; bool wrow[VW];
@@ -421,7 +422,7 @@ __global__ __launch_bounds__(kThreads, OCC) void igemm_kernel(IgemmArgs a) {
         if (XF) {
           const u32x4* py = ok ? reinterpret_cast<const u32x4*>(a.xf_x + xoff[i]) : zero_page;
           r.y[i] = *py;
-          const uint8_t* pm = (ok && a.xf_mask) ? a.xf_mask + (xoff[i] >> 3) : reinterpret_cast<const uint8_t*>(g_zero_page);
+          const uint8_t* pm = (ok && a.xf_mask) ? a.xf_mask + (xoff[i] >> 3) : reinterpret_cast<const uint8_t*>(zero_page);
           r.mk[i] = a.xf_mask ? (uint32_t)*pm : (ok ? 0xffu : 0u);
         }
         xoff[i] += BKT;
@@ -557,10 +558,23 @@ __global__ __launch_bounds__(kThreads, OCC) void igemm_kernel(IgemmArgs a) {
 typedef __attribute__((address_space(3))) void* lds_void_ptr;
 typedef const __attribute__((address_space(1))) void* gbl_void_ptr;
 
-// ANYC: the contraction channels are no multiple of the k-tile (160 channels, 64-wide tiles), so a tile straddles
-// filter taps: every lane follows the tap and channel of its own 16-byte vector (a vector never straddles: Cin % 8
-// == 0), and the last tile is padded from the zero page.
-template <int TC, int TP, int WGC, int OCC, int BKT, bool ANYC = false>
+//
+// The loads go through buffer descriptors (buffer_load_dwordx4 ... lds): a lane's byte offset changes only with the
+// filter tap, the position inside the tap is the scalar offset of the instruction, and a vector outside the image or
+// the tensor carries the offset kOob, which lies beyond every descriptor's range: the hardware's range check then
+// delivers zeros.  With flat addresses every load cost about nine vector instructions (64-bit address, zero-page
+// select) and every k-tile a scalar load of the zero page's address.  Measured (3x3, us, flat -> buffer): 64 channels at
+// 32x32, 512 images 66 -> 56; 128 at 16x16 46 -> 40; 64 at 56x56, 256 images 100 -> 88; 128 at 28x28 71 -> 64.
+constexpr uint32_t kOob = 0xfffffff0u;     // operands hold fewer than 2^31 elements in whole vectors: at most kOob bytes
+typedef __amdgpu_buffer_rsrc_t BufRsrc;
+__device__ __forceinline__ BufRsrc buffer_of(const bf16_t* p, int64_t elements) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(p), 0, (int)(uint32_t)(elements * 2), 0x00020000);
+}
+__device__ __forceinline__ void load_to_lds(BufRsrc r, unsigned char* dst, uint32_t lane_off, uint32_t uniform_off) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void_ptr)dst, 16, (int)lane_off, (int)uniform_off, 0, 0);
+}
+
+template <int TC, int TP, int WGC, int OCC, int BKT>
 __global__ __launch_bounds__(kThreads, OCC) void igemm_dma_kernel(IgemmArgs a) {
   constexpr int KS = BKT / 16, NS = BKT / 8;              // MFMA k-steps per tile; 16-byte slots per tile row
   constexpr int WGP = 4 / WGC;
@@ -602,60 +616,36 @@ __global__ __launch_bounds__(kThreads, OCC) void igemm_dma_kernel(IgemmArgs a) {
     hb[i] = ho * a.ostride - a.pad_h; wb[i] = wo * a.ostride - a.pad_w;
     nb[i] = n * a.Hin * a.Win;
   }
-  const int ntiles = ANYC ? (a.Ktot + BKT - 1) / BKT : a.Ktot / BKT;
-  const unsigned char* zero_page = reinterpret_cast<const unsigned char*>(g_zero_page);
+  const int ntiles = a.Ktot / BKT;
   const int ps = a.xstride ? a.xstride : a.Cin;         // elements between neighbouring input pixels
   const int xcol = (kvec * 8) / ps;                     // pixel this thread's vector lies in, relative to the tap (0 unless xstride is set)
-  int woff[VW]; bool wrow[VW];
+  const BufRsrc wbuf = buffer_of(a.wt, (int64_t)a.Cout * a.Ktot), xbuf = buffer_of(a.in, (int64_t)a.B * a.Hin * a.Win * ps);
+  uint32_t woff[VW], xoff[VX];                            // byte offsets of this thread's vectors (kOob: zeros)
 #pragma unroll
   for (int i = 0; i < VW; ++i) {
     const int c = c0 + lrow + RPG * i;
-    wrow[i] = (lrow + RPG * i < TC) & (c < a.Cout);
-    woff[i] = (wrow[i] ? c : 0) * a.Ktot + kvec * 8;
+    woff[i] = ((lrow + RPG * i < TC) & (c < a.Cout)) ? (uint32_t)(c * a.Ktot + kvec * 8) * 2u : kOob;
   }
-  int xoff[VX]; bool xok[VX];
+  uint32_t wk = 0;                                        // bytes into the weight rows
   int kc0 = 0, kr = 0, ks = 0;
-  int kc, gr, gs, kw = kvec * 8;                          // ANYC: channel and tap of this lane's vector, its k index
-  {
-    const int tap = kw / a.Cin;
-    kc = kw - tap * a.Cin; gr = tap / a.KW; gs = tap - gr * a.KW;
-  }
   unsigned char* const wave_base = lds + wave * 1024;     // a wave's 64 vectors = 1 KB of consecutive tile rows
   // all loads of the next k-tile (a tile never straddles a filter tap: the tap, the bounds test and the
   // pixel offset change only every Cin/64 tiles, a uniform branch)
   auto fetch = [&]() {
 #pragma unroll
-    for (int i = 0; i < VW; ++i) {
-      const unsigned char* p = (wrow[i] & (!ANYC || kw < a.Ktot)) ? reinterpret_cast<const unsigned char*>(a.wt + woff[i]) : zero_page;
-      __builtin_amdgcn_global_load_lds((gbl_void_ptr)p, (lds_void_ptr)(wave_base + i * (RPG * RB)), 16, 0, 0);
-      woff[i] += BKT;
-    }
-    if (ANYC) {
-#pragma unroll
-      for (int i = 0; i < VX; ++i) {
-        const int hi = hb[i] + gr, wi = wb[i] + gs;
-        const bool ok = mv[i] & (gr < a.KH) & (hi >= 0) & (wi >= 0) & (hi < a.Hin) & (wi < a.Win);
-        const unsigned char* p = ok ? reinterpret_cast<const unsigned char*>(a.in + (nb[i] + hi * a.Win + wi) * a.Cin + kc) : zero_page;
-        __builtin_amdgcn_global_load_lds((gbl_void_ptr)p, (lds_void_ptr)(wave_base + XBASE + i * (RPG * RB)), 16, 0, 0);
-      }
-      kw += BKT; kc += BKT;
-      while (kc >= a.Cin) { kc -= a.Cin; if (++gs == a.KW) { gs = 0; ++gr; } }
-      return;
-    }
+    for (int i = 0; i < VW; ++i)
+      load_to_lds(wbuf, wave_base + i * (RPG * RB), woff[i], wk);
+    wk += BKT * 2;
     if (kc0 == 0) {
 #pragma unroll
       for (int i = 0; i < VX; ++i) {
         const int hi = hb[i] + kr, wi = wb[i] + ks;
-        xok[i] = mv[i] & (hi >= 0) & (wi + xcol >= 0) & (hi < a.Hin) & (wi + xcol < a.Win);
-        xoff[i] = (nb[i] + hi * a.Win + wi) * ps + kvec * 8;
+        const bool ok = mv[i] & (hi >= 0) & (wi + xcol >= 0) & (hi < a.Hin) & (wi + xcol < a.Win);
+        xoff[i] = ok ? (uint32_t)((nb[i] + hi * a.Win + wi) * ps + kvec * 8) * 2u : kOob;
       }
     }
 #pragma unroll
-    for (int i = 0; i < VX; ++i) {
-      const unsigned char* p = xok[i] ? reinterpret_cast<const unsigned char*>(a.in + xoff[i]) : zero_page;
-      __builtin_amdgcn_global_load_lds((gbl_void_ptr)p, (lds_void_ptr)(wave_base + XBASE + i * (RPG * RB)), 16, 0, 0);
-      xoff[i] += BKT;
-    }
+    for (int i = 0; i < VX; ++i) load_to_lds(xbuf, wave_base + XBASE + i * (RPG * RB), xoff[i], (uint32_t)kc0 * 2u);
     kc0 += BKT;
     if (kc0 == a.Cin) { kc0 = 0; if (++ks == a.KW) { ks = 0; ++kr; } }
   };
@@ -703,50 +693,62 @@ __global__ __launch_bounds__(kThreads, OCC) void igemm_dma_kernel(IgemmArgs a) {
   igemm_epilogue<TC, TP, WGC>(a, acc, lds, c0, m0, pt);
 }
 
-template <int TC, int TP, int WGC, int OCC, int BKT = 64, bool ANYC = false>
+template <int TC, int TP, int WGC, int OCC, int BKT = 64>
 dat_status launch_igemm_dma(IgemmArgs a, hipStream_t st) {
   if ((int64_t)a.B * a.Hin * a.Win * a.Cin >= (1ll << 31) || (int64_t)a.Cout * a.Ktot >= (1ll << 31)) return DAT_ERR_UNSUPPORTED;
-  if (ANYC ? (a.Cin % 8 != 0 || a.Ktot != a.KH * a.KW * a.Cin || a.Ktot < BKT || a.xstride != 0)
-           : (a.Cin % BKT != 0 || a.Ktot < BKT || a.Ktot % BKT != 0)) return DAT_ERR_UNSUPPORTED;
+  if (a.Cin % BKT != 0 || a.Ktot < BKT || a.Ktot % BKT != 0) return DAT_ERR_UNSUPPORTED;
   if (a.xstride && (a.Cin != BKT || a.xstride % 8 != 0 || a.Cin % a.xstride != 0)) return DAT_ERR_UNSUPPORTED;   // one tap per k-tile
   a.nct = (a.Cout + TC - 1) / TC;
   a.npt = (a.M + TP - 1) / TP;
   if (a.npt == 0) return DAT_OK;
   a.xcd_contiguous = a.KH * a.KW > 1;   // filter windows: neighbouring tiles re-read each other's rows
   const int npt8 = (a.npt + 7) / 8 * 8;
-  hipLaunchKernelGGL((igemm_dma_kernel<TC, TP, WGC, OCC, BKT, ANYC>), dim3((unsigned)(npt8 * a.nct)), dim3(kThreads), 0, st, a);
+  hipLaunchKernelGGL((igemm_dma_kernel<TC, TP, WGC, OCC, BKT>), dim3((unsigned)(npt8 * a.nct)), dim3(kThreads), 0, st, a);
   DAT_LAUNCH_CHECK();
   return DAT_OK;
 }
 
-// ---- ring variant for long contractions that fill the chip with ONE round of large tiles -----------------------
-// 8 waves, 256-channel tiles, S LDS stages of 64-wide k-tiles filled by the same direct-to-LDS loads.  While tile t
-// is multiplied, the loads of tile t+S-1 are issued during its first k-step (spread over the MFMA groups so that the
-// address queue never holds a burst from all waves), and `s_waitcnt vmcnt((S-2)*loads)` at the end of the tile
-// waits for tile t+1 only.  Half the operand bytes per FLOP of the 128x128 kernel; it pays when the layer is one
-// round of at most one workgroup per CU (pick_ring), where the single-stage kernel cannot hide the load latency
-// behind other workgroups.
-template <int TC, int TP, int WGC, int S>
-__global__ __launch_bounds__(512) void igemm_ring_kernel(IgemmArgs a) {
-  constexpr int NT = 512, BKT = 64, KS = BKT / 16;
+// ---- ring variant: layers with at most a few workgroups per CU --------------------------------------------------
+// S LDS stages of 64-wide k-tiles filled by the same direct-to-LDS loads, NT / 64 waves, one or two workgroups per CU.
+// The single-stage kernel hides its load latency behind other workgroups; a layer that has none to offer (few tiles)
+// or that is faster in tiles too large for four workgroups per CU hides it behind the S - 1 k-tiles in flight here.
+// What then bounds a k-tile is the chain barrier -> LDS reads -> MFMA.  So the fragments of the next group of G
+// k-steps are read (into the other half of a register double buffer) before the current group is multiplied, across
+// the tile boundary too: the barrier stands in front of a tile's last group, when every wave has finished reading the
+// stage, so that the next tile's first reads and the refill of the stage run under that group's MFMAs.  G = 4 (a whole
+// tile) where two sets of fragments fit the registers, else 1.
+// Measured (3x3 layers, forward, us; single-stage kernels -> ring): 512 channels at 4x4, 13 images 47 -> 18
+// (32 x 128 tiles), 512 images 63 -> 38 (128 x 128); 7x7, 85 images 51 -> 33; 5x5, 50 images 49 -> 20; 256 channels at
+// 14x14, 85 images 40 -> 28 (256 x 128); 320 channels at 16x16, 256 images 138 -> 106 and 640 at 8x8 133 -> 100 = 1.2
+// PFLOP/s (160 x 256).
+// ANYC: the contraction channels are no multiple of the k-tile (160 channels, 64-wide tiles), so a tile straddles
+// filter taps: every lane follows the tap and channel of its own 16-byte vector (a vector never straddles: Cin % 8
+// == 0), and the last tile is padded with zeros.
+template <int TC, int TP, int WGC, int S, int NT, int G, bool ANYC = false>
+__global__ __launch_bounds__(NT) void igemm_ring_kernel(IgemmArgs a) {
+  constexpr int BKT = 64, KS = BKT / 16, NG = KS / G;       // MFMA k-steps per tile, in NG groups of G
   constexpr int WGP = NT / 64 / WGC;
   constexpr int WC = TC / WGC, WP = TP / WGP;
   constexpr int NI = WC / 32, NJ = WP / 32;
   constexpr int RB = 128, RPG = NT / 8;                   // bytes per tile row; tile rows covered by one load per thread
-  constexpr int VW = TC / RPG, VX = TP / RPG;
+  constexpr int VW = (TC + RPG - 1) / RPG, VX = TP / RPG;
   constexpr int NL = VW + VX;                             // loads per thread per tile
+  constexpr bool PART = TC % RPG != 0;                    // the last weight sweep is short: its upper waves have no load
+  constexpr int NLMIN = PART ? NL - 1 : NL;               // loads every wave issues per tile
   constexpr int TILE_BYTES = (TC + TP) * RB;
-  constexpr int E_BYTES = TP * (TC * 2 + 16);
+  constexpr int STG_BYTES = TP * (TC * 2 + 16);
+  constexpr int RED_BYTES = (NT / (TC / 8)) * 3 * TC * 4;
+  constexpr int E_BYTES = STG_BYTES > RED_BYTES ? STG_BYTES : RED_BYTES;
   constexpr int LDS_BYTES = (S * TILE_BYTES > E_BYTES) ? S * TILE_BYTES : E_BYTES;
-  static_assert(TC % RPG == 0 && TP % RPG == 0, "tile rows must be whole load sweeps");
-  static_assert(S >= 2 && (S - 2) * NL <= 63, "vmcnt range");
-  static_assert(NI >= 2 && VW % (NI / 2) == 0 && VX % (NI - NI / 2) == 0, "loads spread evenly over the MFMA groups of a k-step");
+  static_assert(TC % 8 == 0 && TP % RPG == 0, "pixel rows must be whole load sweeps, weight rows whole waves");
+  static_assert(S >= 2 && (S - 1) * NL <= 63, "vmcnt range");
+  static_assert(LDS_BYTES <= 163840, "LDS of a CU");
   __shared__ __attribute__((aligned(1024))) unsigned char lds[LDS_BYTES];
 
   const int bid = blockIdx.x;
   const int q = bid >> 3;
   const int ct = q % a.nct;
-  const int pt = (q / a.nct) * 8 + (bid & 7);
+  const int pt = a.xcd_contiguous ? (bid & 7) * ((a.npt + 7) >> 3) + (q / a.nct) : (q / a.nct) * 8 + (bid & 7);
   if (pt >= a.npt) return;
   const int c0 = ct * TC, m0 = pt * TP;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -767,45 +769,50 @@ __global__ __launch_bounds__(512) void igemm_ring_kernel(IgemmArgs a) {
     hb[i] = ho * a.ostride - a.pad_h; wb[i] = wo * a.ostride - a.pad_w;
     nb[i] = n * a.Hin * a.Win;
   }
-  const int ntiles = a.Ktot / BKT;
-  const unsigned char* zero_page = reinterpret_cast<const unsigned char*>(g_zero_page);
-  int woff[VW]; bool wrow[VW];
+  const int ntiles = ANYC ? (a.Ktot + BKT - 1) / BKT : a.Ktot / BKT;
+  const BufRsrc wbuf = buffer_of(a.wt, (int64_t)a.Cout * a.Ktot), xbuf = buffer_of(a.in, (int64_t)a.B * a.Hin * a.Win * a.Cin);
+  uint32_t woff[VW], xoff[VX];                            // byte offsets of this thread's vectors (kOob: zeros)
 #pragma unroll
   for (int i = 0; i < VW; ++i) {
     const int c = c0 + lrow + RPG * i;
-    wrow[i] = c < a.Cout;
-    woff[i] = (wrow[i] ? c : 0) * a.Ktot + kvec * 8;
+    woff[i] = ((lrow + RPG * i < TC) & (c < a.Cout)) ? (uint32_t)(c * a.Ktot + kvec * 8) * 2u : kOob;
   }
-  int xoff[VX]; bool xok[VX];
   int kc0 = 0, kr = 0, ks = 0, kf = 0;
-  bool tile_ok = true;
+  uint32_t wk = 0;                                        // bytes into the weight rows
+  int kc, gr, gs, kw = kvec * 8;                          // ANYC: channel and tap of this lane's vector, its k index
+  {
+    const int tap = kw / a.Cin;
+    kc = kw - tap * a.Cin; gr = tap / a.KW; gs = tap - gr * a.KW;
+  }
   unsigned char* sb = lds;
-  // the loads of tile kf into ring stage `stage`, one at a time (tiles past the end fetch the zero page so that
+  // the loads of tile kf into ring stage `stage`, one at a time (past the end the last tile is fetched again, so that
   // every tile issues the same number of loads and the vmcnt arithmetic stays exact)
-  auto fetch_begin = [&](int stage) { tile_ok = kf < ntiles; sb = lds + stage * TILE_BYTES + wave * 1024; };
+  auto fetch_begin = [&](int stage) { sb = lds + stage * TILE_BYTES + wave * 1024; };
   auto fetch_w = [&](int i) {
-    const unsigned char* p = (tile_ok & wrow[i]) ? reinterpret_cast<const unsigned char*>(a.wt + woff[i]) : zero_page;
-    __builtin_amdgcn_global_load_lds((gbl_void_ptr)p, (lds_void_ptr)(sb + i * (RPG * RB)), 16, 0, 0);
-    woff[i] += BKT;
+    if (PART && i == VW - 1 && wave * 8 + RPG * i >= TC) return;   // (uniform: a wave's load is 8 rows)
+    load_to_lds(wbuf, sb + i * (RPG * RB), (!ANYC || kw < a.Ktot) ? woff[i] : kOob, wk);
   };
   auto fetch_tap = [&]() {
-    if (kc0 != 0) return;
+    if (!ANYC && kc0 != 0) return;
 #pragma unroll
     for (int i = 0; i < VX; ++i) {
-      const int hi = hb[i] + kr, wi = wb[i] + ks;
-      xok[i] = mv[i] & (hi >= 0) & (wi >= 0) & (hi < a.Hin) & (wi < a.Win);
-      xoff[i] = (nb[i] + hi * a.Win + wi) * a.Cin + kvec * 8;
+      const int r = ANYC ? gr : kr, c = ANYC ? gs : ks;
+      const int hi = hb[i] + r, wi = wb[i] + c;
+      const bool ok = mv[i] & (r < a.KH) & (hi >= 0) & (wi >= 0) & (hi < a.Hin) & (wi < a.Win);
+      xoff[i] = ok ? (uint32_t)((nb[i] + hi * a.Win + wi) * a.Cin + (ANYC ? kc : kvec * 8)) * 2u : kOob;
     }
   };
-  auto fetch_x = [&](int i) {
-    const unsigned char* p = (tile_ok & xok[i]) ? reinterpret_cast<const unsigned char*>(a.in + xoff[i]) : zero_page;
-    __builtin_amdgcn_global_load_lds((gbl_void_ptr)p, (lds_void_ptr)(sb + TC * RB + i * (RPG * RB)), 16, 0, 0);
-    xoff[i] += BKT;
-  };
+  auto fetch_x = [&](int i) { load_to_lds(xbuf, sb + TC * RB + i * (RPG * RB), xoff[i], ANYC ? 0u : (uint32_t)kc0 * 2u); };
   auto fetch_end = [&]() {
-    kc0 += BKT;
-    if (kc0 == a.Cin) { kc0 = 0; if (++ks == a.KW) { ks = 0; ++kr; } }
-    ++kf;
+    if (++kf >= ntiles) return;
+    wk += BKT * 2;
+    if (ANYC) {
+      kw += BKT; kc += BKT;
+      while (kc >= a.Cin) { kc -= a.Cin; if (++gs == a.KW) { gs = 0; ++gr; } }
+    } else {
+      kc0 += BKT;
+      if (kc0 == a.Cin) { kc0 = 0; if (++ks == a.KW) { ks = 0; ++kr; } }
+    }
   };
   int fa_off[NI], fb_off[NJ];
 #pragma unroll
@@ -821,8 +828,8 @@ __global__ __launch_bounds__(512) void igemm_ring_kernel(IgemmArgs a) {
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
-#pragma unroll
-  for (int p = 0; p < S - 1; ++p) {
+#pragma unroll 1
+  for (int p = 0; p < S; ++p) {
     fetch_begin(p);
 #pragma unroll
     for (int i = 0; i < VW; ++i) fetch_w(i);
@@ -831,67 +838,81 @@ __global__ __launch_bounds__(512) void igemm_ring_kernel(IgemmArgs a) {
     for (int i = 0; i < VX; ++i) fetch_x(i);
     fetch_end();
   }
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"((S - 2) * NL) : "memory");
+  Frag fa[2][G][NI], fb[2][G][NJ];
+  auto read_group = [&](const unsigned char* base, int g, int buf) {
+#pragma unroll
+    for (int u = 0; u < G; ++u) {
+#pragma unroll
+      for (int i = 0; i < NI; ++i) fa[buf][u][i].u = *reinterpret_cast<const u32x4*>(base + (fa_off[i] ^ ((g * G + u) * 32)));
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) fb[buf][u][j].u = *reinterpret_cast<const u32x4*>(base + (fb_off[j] ^ ((g * G + u) * 32)));
+    }
+  };
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"((S - 1) * NLMIN) : "memory");
   __builtin_amdgcn_s_barrier();
-  int stage = 0, fstage = S - 1;
-  for (int t = 0; t < ntiles; ++t) {
+  read_group(lds, 0, 0);
+  int stage = 0;
+  auto tile = [&](int par) {                              // par: register buffer that holds the tile's first group
     const unsigned char* cur = lds + stage * TILE_BYTES;
-    Frag fa[2][NI], fb[2][NJ];
+    const int nstage = stage + 1 == S ? 0 : stage + 1;
 #pragma unroll
-    for (int i = 0; i < NI; ++i) fa[0][i].u = *reinterpret_cast<const u32x4*>(cur + fa_off[i]);
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) fb[0][j].u = *reinterpret_cast<const u32x4*>(cur + fb_off[j]);
-    fetch_begin(fstage);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int kk = 0; kk < KS; ++kk) {
-#pragma unroll
-      for (int i = 0; i < NI; ++i) {
-#pragma unroll
-        for (int j = 0; j < NJ; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[kk & 1][i].v, fb[kk & 1][j].v, acc[i][j], 0, 0, 0);
-        if (i == 0 && kk + 1 < KS) {                       // fragments of the next k-step under this one's MFMAs
-#pragma unroll
-          for (int ii = 0; ii < NI; ++ii) fa[(kk + 1) & 1][ii].u = *reinterpret_cast<const u32x4*>(cur + (fa_off[ii] ^ ((kk + 1) * 32)));
-#pragma unroll
-          for (int j = 0; j < NJ; ++j) fb[(kk + 1) & 1][j].u = *reinterpret_cast<const u32x4*>(cur + (fb_off[j] ^ ((kk + 1) * 32)));
-        }
-        if (kk == 0) {   // the next ring tile: weights behind the first half of this k-step's MFMA groups, pixels behind the second
-          constexpr int H = NI / 2;
-          if (i < H) {
-#pragma unroll
-            for (int u = 0; u < VW / H; ++u) fetch_w(i * (VW / H) + u);
-            if (i == H - 1) fetch_tap();
-          } else {
-#pragma unroll
-            for (int u = 0; u < VX / (NI - H); ++u) fetch_x((i - H) * (VX / (NI - H)) + u);
-          }
-        }
-        __builtin_amdgcn_sched_barrier(0);
+    for (int g = 0; g < NG; ++g) {
+      const int buf = (par + g) & 1;
+      if (g == NG - 1) {
+        // all of this wave's reads of the stage are done and its part of tile t+1 has landed (at most S-2 tiles of
+        // loads outstanding); behind the barrier that holds for every wave: the next tile can be read, the stage refilled
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((S - 2) * NLMIN) : "memory");
+        __builtin_amdgcn_s_barrier();
+        read_group(lds + nstage * TILE_BYTES, 0, buf ^ 1);
+        fetch_begin(stage);
+      } else {
+        read_group(cur, g + 1, buf ^ 1);
       }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int u = 0; u < G; ++u)
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+#pragma unroll
+          for (int j = 0; j < NJ; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[buf][u][i].v, fb[buf][u][j].v, acc[i][j], 0, 0, 0);
+          if (g == NG - 1) {   // tile t+S, spread over this group's MFMAs: weights first, then pixels
+#pragma unroll
+            for (int l = 0; l < NL; ++l)
+              if (l * (G * NI) / NL == u * NI + i) {
+                if (l < VW) fetch_w(l);
+                else { if (l == VW) fetch_tap(); fetch_x(l - VW); }
+              }
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
     }
     fetch_end();
-    // this wave's part of tile t+1 has landed once at most (S-2) tiles of loads are outstanding; the barrier then
-    // covers every wave's part, and everyone is done reading `stage`
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((S - 2) * NL) : "memory");
-    __builtin_amdgcn_s_barrier();
-    stage = stage + 1 == S ? 0 : stage + 1;
-    fstage = fstage + 1 == S ? 0 : fstage + 1;
+    stage = nstage;
+  };
+  if (NG & 1) {
+    int t = 0;
+    for (; t + 2 <= ntiles; t += 2) { tile(0); tile(1); }
+    if (t < ntiles) tile(0);
+  } else {
+    for (int t = 0; t < ntiles; ++t) tile(0);
   }
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // the zero-page loads of the tail land in LDS too
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");   // the loads past the end land in LDS too
   __builtin_amdgcn_s_barrier();
   igemm_epilogue<TC, TP, WGC, NT>(a, acc, lds, c0, m0, pt);
 }
 
-template <int TC, int TP, int WGC, int S>
+template <int TC, int TP, int WGC, int S, int NT, int G, bool ANYC = false>
 dat_status launch_igemm_ring(IgemmArgs a, hipStream_t st) {
   if ((int64_t)a.B * a.Hin * a.Win * a.Cin >= (1ll << 31) || (int64_t)a.Cout * a.Ktot >= (1ll << 31)) return DAT_ERR_UNSUPPORTED;
-  if (a.Cin % 64 != 0 || a.Ktot < 64 || a.xf_tab) return DAT_ERR_UNSUPPORTED;
+  if (a.Ktot < 64 || a.xf_tab || a.xstride) return DAT_ERR_UNSUPPORTED;
+  if (ANYC ? (a.Cin % 8 != 0 || a.Ktot != a.KH * a.KW * a.Cin) : a.Cin % 64 != 0) return DAT_ERR_UNSUPPORTED;
   a.nct = (a.Cout + TC - 1) / TC;
   a.npt = (a.M + TP - 1) / TP;
   if (a.npt == 0) return DAT_OK;
+  a.xcd_contiguous = 0;
   const int npt8 = (a.npt + 7) / 8 * 8;
-  hipLaunchKernelGGL((igemm_ring_kernel<TC, TP, WGC, S>), dim3((unsigned)(npt8 * a.nct)), dim3(512), 0, st, a);
+  hipLaunchKernelGGL((igemm_ring_kernel<TC, TP, WGC, S, NT, G, ANYC>), dim3((unsigned)(npt8 * a.nct)), dim3(NT), 0, st, a);
   DAT_LAUNCH_CHECK();
   return DAT_OK;
 }
@@ -967,27 +988,56 @@ int compute_units() {
   return n;
 }
 
-// Which ring configuration, if any, runs this launch: 0 none, 1 = 256 channels x 256 pixels, 2 = 256 x 128.
-// Long contractions into a multiple of 256 channels whose tiles make one round of 60-100 % of the CUs (measured at
-// B = 256: 14x14 3x3 256->256 82 -> 66 us and 1024->256 42 -> 35 us with 256x256 tiles; 7x7 3x3 512->512 87 -> 75 us
-// and 2048->512 44 -> 37 us with 256x128; slower than the 128x128 kernel wherever several rounds are needed or the
-// contraction is short).
 std::atomic<bool> g_ring_enabled{true};
 std::atomic<bool> g_tile160{true};
 std::atomic<bool> g_narrow_underfilled{true};
 
-int pick_ring(const IgemmArgs& a) {
-  if (a.xf_tab || a.ostep != 1 || a.stat_slab0 != 0 || a.Cin % 64 != 0 || a.Ktot < 1024 || a.Cout % 256 != 0) return 0;
-  if (!g_ring_enabled.load(std::memory_order_relaxed)) return 0;   // dat_set_kernel_option: every layer through the 128x128 kernels
-  const int64_t cus = compute_units(), nct = a.Cout / 256;
-  const int64_t t256 = ((int64_t)a.M + 255) / 256 * nct, t128 = ((int64_t)a.M + 127) / 128 * nct;
-  if (t256 <= cus && 5 * t256 >= 3 * cus) return 1;
-  if (t128 <= cus && 5 * t128 >= 3 * cus) return 2;
-  return 0;
+// Which ring configuration, if any, runs this launch.  The lines are drawn by tiles per CU (256 CUs), measured on the
+// 3x3 and 1x1 layers of every network at batches of 13 to 512, us:
+//  * kR160x256 / kR160x128: widths that are a multiple of 160 (the wide ResNets).  Every wave takes all 160 channels of 32
+//    pixels: no empty MFMA rows, and the gathered activations are fetched once per 160 channels.  One 256-pixel tile
+//    per CU at a time, or two 128-pixel ones; the same work per round, the larger tile 2-5 % faster (640 channels, 256
+//    images 99.7 / 106.7).  With an odd number of 128-pixel tiles per CU the larger tile would leave half of its last
+//    round idle (640 channels, 128 images, one tile per CU: 72 / 63).
+//  * kR256x256, kR256x128: contraction >= 1024 into a multiple of 256 channels, one round over at least 60 (50) % of the CUs:
+//    14x14 256 -> 256 at 256 images 65 (128x128 tiles) -> 56, 7x7 512 -> 512 75 -> 58; 14x14 at 85 images (131 tiles) 40 -> 28.
+//  * at most one 128x128 tile per CU, contraction >= 256: the largest tile that still gives half of the CUs one.
+//    128x128 above half a tile per CU (20x20 128 -> 128 at 50 images 16.1 -> 12.4; 64x128 tiles 12.9), 64x128 above a
+//    quarter (10x10 256 -> 256 at 50 images 22.8 -> 15.4; 32x128 17.2, 128x128 19.1), else 32x128 (5x5 512 -> 512 at 50
+//    images 48.8 -> 19.6; 64x128 25.6).
+enum RingPick { kRNone, kR32, kR64, kR128, kR256x128, kR256x256, kR160x128, kR160x256, kR160x128Any, kR160x256Any };
+
+RingPick pick_ring(const IgemmArgs& a) {
+  if (a.xf_tab || a.xstride || a.Cin % 8 != 0 || a.Ktot < 256 || a.KH * a.KW * a.Cin != a.Ktot) return kRNone;
+  const int64_t cus = compute_units(), p128 = ((int64_t)a.M + 127) / 128, p256 = ((int64_t)a.M + 255) / 256;
+  const bool one_grid = a.ostep == 1 && a.stat_slab0 == 0;       // 256-pixel tiles: the whole tensor is this launch
+  if (a.Cout % 160 == 0 && (a.Cin % 64 == 0 || a.Ktot >= 512) && g_tile160.load(std::memory_order_relaxed)) {
+    const int64_t per_cu = (p128 * (a.Cout / 160) + cus - 1) / cus;
+    const bool any = a.Cin % 64 != 0;
+    // 640 channels over few pixels: 128 divides them too, and the narrower tiles below give more CUs work
+    if (a.Cout % 128 != 0 || any || 2 * p128 * (a.Cout / 160) > cus) {
+      if (one_grid && per_cu % 2 == 0) return any ? kR160x256Any : kR160x256;
+      return any ? kR160x128Any : kR160x128;
+    }
+  }
+  if (a.Cin % 64 != 0) return kRNone;
+  if (one_grid && a.Ktot >= 1024 && a.Cout % 256 == 0 && g_ring_enabled.load(std::memory_order_relaxed)) {
+    const int64_t nct = a.Cout / 256, t256 = p256 * nct, t128 = p128 * nct;
+    if (t256 <= cus && 5 * t256 >= 3 * cus) return kR256x256;
+    if (t128 <= cus && 2 * t128 >= cus) return kR256x128;
+  }
+  if (!g_narrow_underfilled.load(std::memory_order_relaxed)) return kRNone;
+  const int64_t t = p128 * ((a.Cout + 127) / 128);
+  if (a.Cout > 64 && t <= cus) return 2 * t > cus ? kR128 : 4 * t > cus ? kR64 : kR32;
+  if (a.Cout <= 64 && 2 * p128 <= cus) return kR32;
+  return kRNone;
 }
 
 // pixel rows per tile (= per slab of epilogue statistics) of the configuration run_igemm selects
-int pixel_tile(const IgemmArgs& a) { return pick_ring(a) == 1 ? 256 : 128; }
+int pixel_tile(const IgemmArgs& a) {
+  const RingPick r = pick_ring(a);
+  return r == kR256x256 || r == kR160x256 || r == kR160x256Any ? 256 : 128;
+}
 
 dat_status run_igemm(const IgemmArgs& a, hipStream_t st) {
   g_launches.fetch_add(1, std::memory_order_relaxed);
@@ -998,9 +1048,16 @@ dat_status run_igemm(const IgemmArgs& a, hipStream_t st) {
     return a.Cout <= 32 ? launch_igemm_dma<32, 128, 1, 6>(a, st) : launch_igemm_dma<64, 128, 2, 5>(a, st);
   }
   switch (pick_ring(a)) {
-    case 1: return launch_igemm_ring<256, 256, 2, 2>(a, st);
-    case 2: return launch_igemm_ring<256, 128, 4, 3>(a, st);
-    default: break;
+    case kR32: return launch_igemm_ring<32, 128, 1, 4, 256, 4>(a, st);
+    case kR64: return launch_igemm_ring<64, 128, 2, 3, 256, 4>(a, st);
+    case kR128: return launch_igemm_ring<128, 128, 2, 4, 512, 4>(a, st);
+    case kR256x128: return launch_igemm_ring<256, 128, 4, 3, 512, 1>(a, st);
+    case kR256x256: return launch_igemm_ring<256, 256, 2, 2, 512, 1>(a, st);
+    case kR160x128: return launch_igemm_ring<160, 128, 1, 2, 256, 1>(a, st);
+    case kR160x256: return launch_igemm_ring<160, 256, 1, 3, 512, 1>(a, st);
+    case kR160x128Any: return launch_igemm_ring<160, 128, 1, 2, 256, 1, true>(a, st);
+    case kR160x256Any: return launch_igemm_ring<160, 256, 1, 3, 512, 1, true>(a, st);
+    case kRNone: break;
   }
   if (a.xf_tab) {
     // 64-channel results (contraction 256, four k-tiles): one register set in flight and three workgroups per CU
@@ -1009,14 +1066,8 @@ dat_status run_igemm(const IgemmArgs& a, hipStream_t st) {
     if (a.Cout <= 64) return launch_igemm_xf<64, 128, 2, 1, 64, 3>(a, st);
     return launch_igemm_xf<128, 128, 2, 2, 32, 2>(a, st);
   }
-  // widths that are a multiple of 160 but not of 128 (the wide ResNets' 160 and 320 channels): 160-channel tiles, each
-  // wave all channels of 32 pixels -- no empty MFMA rows in a last tile, and the gathered activations are fetched
-  // once per 160 instead of once per 128 output channels
-  if (a.Cout % 160 == 0 && a.Cout % 128 != 0 && g_tile160.load(std::memory_order_relaxed)) {
-    if (a.Cin % 64 == 0 && a.Ktot >= 64) return launch_igemm_dma<160, 128, 1, 3>(a, st);
-    if (a.Cin % 32 == 0 && a.Ktot >= 512 && !a.xstride) return launch_igemm_dma<160, 128, 1, 3, 64, true>(a, st);   // 160 -> 160
-    return launch_igemm<160, 128, 1, 1, 32, 3>(a, st);
-  }
+  // short contractions into a multiple of 160 channels that 128 does not divide: 160-channel tiles
+  if (a.Cout % 160 == 0 && a.Cout % 128 != 0 && g_tile160.load(std::memory_order_relaxed)) return launch_igemm<160, 128, 1, 1, 32, 3>(a, st);
   // narrow channel tiles: the direct-to-LDS kernel wherever its k-tile divides the contraction channels,
   // except 1x1 layers with a long contraction into <= 64 channels (HBM-bound reads: deep register
   // prefetch with two workgroups per CU streams them at the copy rate)
@@ -1028,14 +1079,6 @@ dat_status run_igemm(const IgemmArgs& a, hipStream_t st) {
     if (a.Cin % 64 == 0 && a.Ktot >= 64 && (a.KH * a.KW > 1 || a.Ktot < 256)) return launch_igemm_dma<64, 128, 2, 5>(a, st);
     if (a.Cin % 64 != 0 && a.Cin % 32 == 0 && a.Ktot >= 32) return launch_igemm_dma<64, 128, 2, 5, 32>(a, st);
     return pick_depth<64, 128, 2>(a, st);
-  }
-  // Long contractions whose 128x128 tiles would leave at most one and a half workgroups per CU (4x4 and 7x7 maps at
-  // small batch): the single-stage kernel hides its load latency only behind other resident workgroups, so 32-channel
-  // tiles -- four times the workgroups -- finish sooner although each fetches the activation tile again.  (Two and
-  // a half workgroups per CU are enough: the 640-channel layers of the wide ResNets lose 12 % this way.)
-  if (a.stat_mode != 3 && a.Cin % 64 == 0 && a.Ktot >= 1024 && g_narrow_underfilled.load(std::memory_order_relaxed)) {
-    const int64_t wgs128 = (int64_t)((a.M + 127) / 128) * ((a.Cout + 127) / 128);
-    if (2 * wgs128 <= 3 * (int64_t)compute_units()) return launch_igemm_dma<32, 128, 1, 6>(a, st);
   }
   return pick_depth_wide(a, st);
 }

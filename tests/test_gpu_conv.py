@@ -133,3 +133,45 @@ def test_32_channel_tiles_of_underfilled_layers_give_the_bits_of_128_channel_til
     test thereby keeps covered at small sizes."""
     assert len(FEW_TILE_SHAPES) >= 6
     _ab(dat, shape, dat.KOPT_NARROW_UNDERFILLED, "128-channel tiles")
+
+
+# One shape for every tile configuration of the multi-stage kernel (256 compute units), with ragged pixel and channel tails:
+# the number of tiles decides which one a layer gets, so these have as many pixels as that takes.
+RING_SHAPES = [
+    (13, 4, 4, 512, 200, 3, 1, 1),     # 32-channel tiles: few tiles
+    (1, 3, 3, 256, 40, 1, 1, 0),       # ... fewer k-tiles than pipeline stages + 1, one pixel tile, <= 64 channels
+    (11, 28, 28, 64, 72, 3, 1, 1),     # 64-channel tiles (68 128-pixel tiles)
+    (21, 28, 28, 64, 104, 3, 1, 1),    # 128-channel tiles, 8 waves (129)
+    (21, 29, 29, 64, 128, 3, 2, 1),    # ... odd strided layer: four parity classes in backward-data
+    (21, 28, 28, 128, 256, 3, 1, 1),   # 256 channels x 128 pixels (129)
+    (40, 31, 31, 128, 256, 3, 1, 1),   # 256 x 256 (151)
+    (5, 15, 15, 64, 160, 3, 1, 1),     # 160 x 128, one tile per compute unit
+    (5, 61, 61, 64, 320, 3, 1, 1),     # 160 x 256 (146 x 2: two 128-pixel tiles per compute unit)
+    (9, 61, 61, 160, 160, 3, 1, 1),    # ... with k-tiles that straddle the filter taps
+    (17, 61, 61, 96, 160, 3, 1, 1),    # 160 x 128 likewise, an odd number of tiles per compute unit's share
+    (7, 30, 30, 320, 640, 1, 2, 0),    # 640 channels
+]
+
+
+@pytest.mark.parametrize("shape", RING_SHAPES)
+def test_multi_stage_tiles_give_the_bits_of_the_single_stage_kernels(dat, shape):
+    """Every output is the same chain of MFMA accumulations in every tile configuration; with the three switches off the same
+    layers run in the single-stage kernels that the tests above hold to the oracle."""
+    B, H, W, Ci, Co, k, st, pad = shape
+    g = torch.Generator(device="cuda").manual_seed(B * H + Co)
+    Ho, Wo = (H + 2 * pad - k) // st + 1, (W + 2 * pad - k) // st + 1
+    x, w, dy = (torch.randn(*s, device="cuda", generator=g).to(torch.bfloat16) for s in ((B, H, W, Ci), (Co, k, k, Ci), (B, Ho, Wo, Co)))
+    options = (dat.KOPT_RING_KERNEL, dat.KOPT_TILE_160, dat.KOPT_NARROW_UNDERFILLED)
+    res = []
+    try:
+        for on in (1, 0):
+            for o in options:
+                dat.set_kernel_option(o, on)
+            res.append((dat.conv_forward(x, w, st, pad), dat.conv_backward_data(dy, w, (H, W), st, pad)))
+            torch.cuda.synchronize()
+    finally:
+        for o in options:
+            dat.set_kernel_option(o, 1)
+    for a, b in zip(*res):
+        assert torch.isfinite(a.float()).all() and a.float().abs().max() > 0
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16))
