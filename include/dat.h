@@ -257,7 +257,8 @@ dat_status dat_conv_backward_weight(const uint16_t* x, const uint16_t* dy, float
  * dat_conv_backward_weight_static_limit() = 32 MiB that is part of the library's device image (each GPU the
  * library runs on holds it until the process ends).  Same arguments, same kernels, same bits as
  * dat_conv_backward_weight.  Returns DAT_ERR_UNSUPPORTED (text in dat_last_error) when the shape's partial sums
- * (splits * Cout*k*k*Cin * 4 bytes; the split count grows with B*Ho*Wo) do not fit, and launches nothing then.
+ * (chains * Cout*k*k*Cin * 4 bytes; the count of chains, ranges of at least 256 output pixels summed in fp32, grows
+ * with B*Ho*Wo up to 2048 over the output tiles) do not fit, and launches nothing then.
  * All calls on one GPU share that buffer: calls that overlap in time on one GPU (different streams or threads)
  * race; calls on one stream are ordered and safe.  Nothing in the buffer needs clearing between calls: every
  * partial sum a call reads was written by its own first launch. */

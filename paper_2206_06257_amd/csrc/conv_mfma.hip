@@ -1191,6 +1191,8 @@ struct WgradArgs {
   float* ws;            // [splits][Cout][Ktot]
   int B, H, W, Cin, Ho, Wo, Cout, k, stride, pad;
   int M, Ktot, pix_per_split;
+  int splits, gx, gy;    // gx x gy output tiles, each summed over `splits` pixel ranges
+  int chunk;             // pixels per chain of fp32 MFMA sums (a multiple of the 64-pixel tile)
 };
 
 // ---- backward-weight through the LDS transpose reads of gfx950 -----------------------------------------------
@@ -1210,8 +1212,17 @@ template <int ROWB> __device__ __forceinline__ int tr_seg_flip(int pixel) {
   return ROWB == 256 ? 2 * (pixel & 3) : 2 * ((pixel >> 1) & 1);     // 256-byte rows: 8 segments; 128-byte rows: 4
 }
 
+//
+// Two workgroups per CU, one round of them: the pixel range is split only as far as that takes, because every split
+// costs a partial tile written and read again (64 KB; with four times the splits that traffic was a third to a half of
+// the whole).  The chain of fp32 sums stays as short as with many splits: every `chunk` pixels the accumulators are
+// added to a second set and start from zero -- the registers for it are there at two workgroups per CU.  All tiles of
+// a pixel range run on one XCD (its L2 then holds both operands), every XCD an eighth of the work.
+// Measured, kernel + reduction, us (2048 workgroups, flat loads -> this): 3x3, 391 images 128 -> 128 at 16x16
+// 101 -> 44, 256 -> 256 at 8x8 74 -> 44; 256 images 64 -> 64 at 56x56 176 -> 92, 256 -> 256 at 14x14 110 -> 72 (830 TFLOP/s);
+// 1x1 1024 -> 256 at 14x14 84 -> 43; 640 -> 640 at 8x8, 128 images 179 -> 78.  Error against 64 bits no larger (1.4e-7 / 1.6e-7).
 template <int TC, int TJ>
-__global__ __launch_bounds__(kThreads, 4) void wgrad_kernel(WgradArgs a) {
+__global__ __launch_bounds__(kThreads, 2) void wgrad_kernel(WgradArgs a) {
   constexpr int BP = 64;                           // pixels per LDS tile
   constexpr int RA = TC * 2, RBJ = TJ * 2;         // bytes per pixel row of the two tiles
   constexpr int CA = RA / 16, CJ = RBJ / 16;       // 16-byte chunks per row
@@ -1219,65 +1230,74 @@ __global__ __launch_bounds__(kThreads, 4) void wgrad_kernel(WgradArgs a) {
   constexpr int WC = TC / 2, WJ = TJ / 2;
   constexpr int NI = WC / 32, NJ = WJ / 32;
   static_assert((RA == 128 || RA == 256) && RBJ == 256, "row swizzles are written for 128- and 256-byte rows");
-  __shared__ __attribute__((aligned(1024))) unsigned char lds[BP * (RA + RBJ)];
-  unsigned char* const abase = lds;
-  unsigned char* const bbase = lds + BP * RA;
+  constexpr int STAGE = BP * (RA + RBJ);
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[2 * STAGE];
 
-  const int c0 = blockIdx.x * TC, j0 = blockIdx.y * TJ;
-  const int split = blockIdx.z;
+  const int tiles = a.gx * a.gy, work = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
+  const int split = work / tiles, tile = work - split * tiles;
+  if (split >= a.splits) return;
+  const int c0 = (tile % a.gx) * TC, j0 = (tile / a.gx) * TJ;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wc = wave & 1, wj = wave >> 1;
   const int p_begin = split * a.pix_per_split;
   const int p_end = min(a.M, p_begin + a.pix_per_split);
   const int HW = a.Ho * a.Wo;
-  const unsigned char* zero_page = reinterpret_cast<const unsigned char*>(g_zero_page);
 
-  // ---- what each of this thread's direct loads fetches: wave instruction q = i*4 + wave fills 1 KB = 64/CA pixel rows
-  int a_pr[NA]; bool a_ok[NA]; int64_t a_off[NA];
-#pragma unroll
-  for (int i = 0; i < NA; ++i) {
-    const int pr = (i * 4 + wave) * (64 / CA) + lane / CA, pc = lane % CA;
-    const int lc = ((((pc >> 1) ^ tr_seg_flip<RA>(pr)) << 1) | (pc & 1));     // logical chunk behind physical chunk pc
-    a_pr[i] = pr;
-    a_ok[i] = c0 + lc * 8 < a.Cout;
-    a_off[i] = (int64_t)(p_begin + pr) * a.Cout + c0 + lc * 8;
-  }
-  int b_pr[NB], b_r[NB], b_s[NB], b_ci[NB], b_n[NB], b_ho[NB], b_wo[NB]; bool b_ok[NB];
-  const int step_q = BP / a.Wo, step_r = BP - step_q * a.Wo;     // 64 pixels further = step_q rows and step_r columns
+  // ---- what this thread's direct loads fetch: wave instruction q = i*4 + wave fills 1 KB = 64/CA (64/CJ) pixel rows.  The
+  // swizzle depends on the low bits of the pixel only, so a thread's channel chunk -- for X its filter tap -- is the
+  // same in all of its loads.  dY rows past the split lie beyond the descriptor's range; an X vector advances by
+  // additions (64 pixels further = step_q rows and step_r columns) and carries kOob where it lies outside the image.
+  const BufRsrc abuf = buffer_of(a.dy + (int64_t)p_begin * a.Cout, (int64_t)(p_end - p_begin) * a.Cout);
+  const BufRsrc bbuf = buffer_of(a.x, (int64_t)a.B * a.H * a.W * a.Cin);
+  const int a_pr = wave * (64 / CA) + lane / CA, a_pc = lane % CA;
+  const int a_lc = ((((a_pc >> 1) ^ tr_seg_flip<RA>(a_pr)) << 1) | (a_pc & 1));     // logical chunk behind physical chunk a_pc
+  const bool a_ok = c0 + a_lc * 8 < a.Cout;
+  uint32_t a_off = (uint32_t)(a_pr * a.Cout + c0 + a_lc * 8) * 2u;
+  const uint32_t a_load_step = (uint32_t)(4 * (64 / CA)) * a.Cout * 2u, a_tile_step = (uint32_t)BP * a.Cout * 2u;
+  const int b_pr = wave * (64 / CJ) + lane / CJ, b_pc = lane % CJ;
+  const int b_lc = ((((b_pc >> 1) ^ tr_seg_flip<RBJ>(b_pr)) << 1) | (b_pc & 1));
+  const int j = j0 + b_lc * 8;
+  const bool b_ok = j < a.Ktot;
+  const int tap = (b_ok ? j : 0) / a.Cin, b_ci = (b_ok ? j : 0) - tap * a.Cin, tap_r = tap / a.k;
+  const int b_r = tap_r - a.pad, b_s = tap - tap_r * a.k - a.pad;
+  const int sh = a.stride - 1;                                    // strides 1 and 2
+  const int step_q = BP / a.Wo, step_r = BP - step_q * a.Wo;
+  const uint32_t px = (uint32_t)a.Cin * 2u, d_col = (uint32_t)a.stride * px, d_row = (uint32_t)a.stride * a.W * px;
+  const uint32_t d_tile = step_q * d_row + step_r * d_col, d_wrap = d_row - a.Wo * d_col, d_image = (uint32_t)a.H * a.W * px - a.Ho * d_row;
+  int b_ho[NB], b_wo[NB]; uint32_t b_off[NB];
 #pragma unroll
   for (int i = 0; i < NB; ++i) {
-    const int pr = (i * 4 + wave) * (64 / CJ) + lane / CJ, pc = lane % CJ;
-    const int lc = ((((pc >> 1) ^ tr_seg_flip<RBJ>(pr)) << 1) | (pc & 1));
-    const int j = j0 + lc * 8;
-    b_pr[i] = pr;
-    b_ok[i] = j < a.Ktot;
-    const int jj = b_ok[i] ? j : 0, tap = jj / a.Cin;
-    b_ci[i] = jj - tap * a.Cin; b_r[i] = tap / a.k; b_s[i] = tap - b_r[i] * a.k;
-    const int p = p_begin + pr;
-    b_n[i] = p / HW; const int rem = p - b_n[i] * HW;
+    const int p = p_begin + b_pr + i * 4 * (64 / CJ);
+    const int n = p / HW, rem = p - n * HW;
     b_ho[i] = rem / a.Wo; b_wo[i] = rem - b_ho[i] * a.Wo;
+    b_off[i] = ((uint32_t)(n * a.H + b_ho[i] * a.stride + b_r) * a.W + b_wo[i] * a.stride + b_s) * px + b_ci * 2;
   }
-  unsigned char* const wave_a = abase + wave * 1024;
-  unsigned char* const wave_b = bbase + wave * 1024;
-  auto fetch = [&](int p0) {
+  auto fetch = [&](int p0, unsigned char* stage) {
+    unsigned char* const wave_a = stage + wave * 1024;
+    unsigned char* const wave_b = wave_a + BP * RA;
 #pragma unroll
-    for (int i = 0; i < NA; ++i) {
-      const bool ok = a_ok[i] && p0 + a_pr[i] < p_end;
-      const unsigned char* src = ok ? reinterpret_cast<const unsigned char*>(a.dy + a_off[i]) : zero_page;
-      __builtin_amdgcn_global_load_lds((gbl_void_ptr)src, (lds_void_ptr)(wave_a + i * 4096), 16, 0, 0);
-      a_off[i] += (int64_t)BP * a.Cout;
-    }
+    for (int i = 0; i < NA; ++i) load_to_lds(abuf, wave_a + i * 4096, a_ok ? a_off + i * a_load_step : kOob, 0);
+    a_off += a_tile_step;
+    const int left = b_ok ? p_end - p0 - b_pr : 0;
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
-      const int hi = b_ho[i] * a.stride + b_r[i] - a.pad, wi = b_wo[i] * a.stride + b_s[i] - a.pad;
-      const bool ok = b_ok[i] && p0 + b_pr[i] < p_end && hi >= 0 && hi < a.H && wi >= 0 && wi < a.W;
-      const unsigned char* src = ok ? reinterpret_cast<const unsigned char*>(a.x + (((int64_t)b_n[i] * a.H + hi) * a.W + wi) * a.Cin + b_ci[i]) : zero_page;
-      __builtin_amdgcn_global_load_lds((gbl_void_ptr)src, (lds_void_ptr)(wave_b + i * 4096), 16, 0, 0);
-      // the same lane's pixel in the next tile
-      b_wo[i] += step_r; b_ho[i] += step_q;
-      if (b_wo[i] >= a.Wo) { b_wo[i] -= a.Wo; ++b_ho[i]; }
-      while (b_ho[i] >= a.Ho) { b_ho[i] -= a.Ho; ++b_n[i]; }
+      const uint32_t hi = (uint32_t)((b_ho[i] << sh) + b_r), wi = (uint32_t)((b_wo[i] << sh) + b_s);
+      const bool ok = (i * 4 * (64 / CJ) < left) & (hi < (uint32_t)a.H) & (wi < (uint32_t)a.W);
+      load_to_lds(bbuf, wave_b + i * 4096, ok ? b_off[i] : kOob, 0);
+    }
+    // the same lane's pixels in the next tile: at most one row wrap, and one image wrap unless an image is smaller than a tile
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      const bool wrap = b_wo[i] + step_r >= a.Wo;
+      b_wo[i] += wrap ? step_r - a.Wo : step_r; b_ho[i] += wrap ? step_q + 1 : step_q; b_off[i] += wrap ? d_tile + d_wrap : d_tile;
+      const bool next = b_ho[i] >= a.Ho;
+      b_ho[i] -= next ? a.Ho : 0; b_off[i] += next ? d_image : 0u;
+    }
+    if (HW < BP) {
+#pragma unroll
+      for (int i = 0; i < NB; ++i)
+        while (b_ho[i] >= a.Ho) { b_ho[i] -= a.Ho; b_off[i] += d_image; }
     }
   };
   // ---- fragment addresses: lane = 16 g + j names pixel 8 (g/2) + j/4 (+ 4 for the second read, + 16 per k-step) and
@@ -1304,31 +1324,56 @@ __global__ __launch_bounds__(kThreads, 4) void wgrad_kernel(WgradArgs a) {
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
+  f32x16 sum[NI][NJ];
+#pragma unroll
+  for (int i = 0; i < NI; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) sum[i][j] = acc[i][j];
+  int chunk_end = p_begin + a.chunk;
+
+  fetch(p_begin, lds);
+  int stage = 0;
   for (int p0 = p_begin; p0 < p_end; p0 += BP) {
-    fetch(p0);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    // this tile has landed, and behind the barrier every wave is done with the other stage
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
+    // all fragments of the tile first, then the next tile's loads (the compiler lets no transpose read pass a direct load
+    // in flight), which land under the MFMAs
+    const unsigned char* cur = lds + stage * STAGE;
+    FragTr fa[BP / 16][NI], fb[BP / 16][NJ];
 #pragma unroll
     for (int kk = 0; kk < BP / 16; ++kk) {
-      FragTr fa[NI], fb[NJ];
 #pragma unroll
       for (int i = 0; i < NI; ++i)
 #pragma unroll
         for (int h = 0; h < 2; ++h)
-          fa[i].h[h] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s16*)(lds + fa_off[i] + (kk * 16 + 4 * h) * RA));
+          fa[kk][i].h[h] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s16*)(cur + fa_off[i] + (kk * 16 + 4 * h) * RA));
 #pragma unroll
       for (int j = 0; j < NJ; ++j)
 #pragma unroll
         for (int h = 0; h < 2; ++h)
-          fb[j].h[h] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s16*)(lds + fb_off[j] + (kk * 16 + 4 * h) * RBJ));
+          fb[kk][j].h[h] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s16*)(cur + fb_off[j] + (kk * 16 + 4 * h) * RBJ));
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (p0 + BP < p_end) fetch(p0 + BP, lds + (stage ^ 1) * STAGE);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int kk = 0; kk < BP / 16; ++kk)
 #pragma unroll
       for (int i = 0; i < NI; ++i)
 #pragma unroll
         for (int j = 0; j < NJ; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i].v, fb[j].v, acc[i][j], 0, 0, 0);
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[kk][i].v, fb[kk][j].v, acc[i][j], 0, 0, 0);
+    stage ^= 1;
+    if (p0 + BP >= chunk_end || p0 + BP >= p_end) {
+      chunk_end += a.chunk;
+#pragma unroll
+      for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) { sum[i][j][e] += acc[i][j][e]; acc[i][j][e] = 0.f; }
     }
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();
   }
   // ---- partial tile -> workspace[split][co][j]   (lane: column j = l%32, rows co = 8g+4h+e)
   float* dst = a.ws + (int64_t)split * a.Cout * a.Ktot;
@@ -1340,7 +1385,7 @@ __global__ __launch_bounds__(kThreads, 4) void wgrad_kernel(WgradArgs a) {
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
         const int co = c0 + wc * WC + i * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
-        if (co < a.Cout && col < a.Ktot) dst[(int64_t)co * a.Ktot + col] = acc[i][j][e];
+        if (co < a.Cout && col < a.Ktot) dst[(int64_t)co * a.Ktot + col] = sum[i][j][e];
       }
     }
 }
@@ -1387,7 +1432,42 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float* __restri
   }
 }
 
-struct WgradPlan { int splits, pix_per_split, gx, gy; bool narrow; };
+// The same for few splits: a thread owns four consecutive elements (one 16-byte load per split) and adds the splits
+// s, s+4, ... into four sums.  Above kFewSplits the loads of one thread are too long a chain.
+constexpr int kFewSplits = 16;
+__global__ __launch_bounds__(256) void wgrad_reduce_few_kernel(const float* __restrict__ ws, int splits, int64_t per_split, int Cin, int cin_real,
+                                                               float scale, float* __restrict__ dw, uint32_t* __restrict__ absmax) {
+  uint32_t* const slot = absmax ? absmax_way(absmax, blockIdx.x) : nullptr;
+  const uint32_t seen = (slot && (threadIdx.x & 63) == 0) ? absmax_peek(slot) : 0u;   // in flight with the loads below
+  const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;                    // (per_split is a multiple of 8)
+  uint32_t m = 0;
+  if (i < per_split) {
+    float4 s[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) s[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int k0 = 0; k0 < splits; k0 += 4) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (k0 + u < splits) {
+          const float4 v = *reinterpret_cast<const float4*>(ws + (int64_t)(k0 + u) * per_split + i);
+          s[u].x += v.x; s[u].y += v.y; s[u].z += v.z; s[u].w += v.w;
+        }
+    }
+    const float r[4] = {((s[0].x + s[1].x) + (s[2].x + s[3].x)) * scale, ((s[0].y + s[1].y) + (s[2].y + s[3].y)) * scale,
+                        ((s[0].z + s[1].z) + (s[2].z + s[3].z)) * scale, ((s[0].w + s[1].w) + (s[2].w + s[3].w)) * scale};
+    const int64_t row = i / Cin; const int ci = (int)(i - row * Cin);                 // (Cin is a multiple of 8: one row)
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (ci + u < cin_real) { dw[row * cin_real + ci + u] = r[u]; m = max(m, abs_bits(r[u])); }
+  }
+  if (absmax) {   // (all 64 lanes of every wavefront reach this point)
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, d));
+    if ((threadIdx.x & 63) == 0) absmax_raise(slot, seen, m);
+  }
+}
+
+struct WgradPlan { int splits, max_splits, pix_per_split, gx, gy, chunk; bool narrow; };   // max_splits: before rounding, grows with the batch
 
 WgradPlan plan_wgrad(const ConvGeom& g) {
   WgradPlan p;
@@ -1397,11 +1477,21 @@ WgradPlan plan_wgrad(const ConvGeom& g) {
   p.gx = (g.Cout + TC - 1) / TC;
   p.gy = (Ktot + 127) / 128;
   const int tiles = p.gx * p.gy;
-  int splits = (2048 + tiles - 1) / tiles;
   const int max_by_pixels = (M + 255) / 256;
-  if (splits > max_by_pixels) splits = max_by_pixels;
+  // pixels per chain of fp32 sums: what about 2048 pieces of work would have
+  int pieces = (2048 + tiles - 1) / tiles;
+  if (pieces > max_by_pixels) pieces = max_by_pixels;
+  if (pieces > 512) pieces = 512;
+  p.chunk = ((M + pieces - 1) / pieces + 63) / 64 * 64;
+  // splits: one round of workgroups.  Two per CU; three of the narrow tiles of a filter window (56x56 64 -> 64 at 256
+  // images 92 us, two 95; the 1x1 layers are bound by HBM and the partial tiles count: 95.7, three 100.7), each at least
+  // five tiles long (50 images of 10x10, 256 -> 256 26.5, with four tiles 28)
+  int splits = (p.narrow && g.k > 1 ? 3 : 2) * compute_units() / tiles;
+  if (splits > (M + 319) / 320) splits = (M + 319) / 320;
   if (splits < 1) splits = 1;
-  if (splits > 512) splits = 512;
+  const int span = (int)((int64_t)M * g.Cout >> 29) + 1;         // a split's dY stays below 2 GiB: 32-bit offsets past its end
+  if (splits < span) splits = span;
+  p.max_splits = splits;
   int pps = (M + splits - 1) / splits;
   pps = (pps + 63) / 64 * 64;
   p.pix_per_split = pps;
@@ -1413,7 +1503,7 @@ WgradPlan plan_wgrad(const ConvGeom& g) {
 
 size_t conv_mfma_wgrad_workspace(const ConvGeom& g) {
   const WgradPlan p = plan_wgrad(g);
-  return (size_t)p.splits * g.Cout * g.k * g.k * g.Cin * sizeof(float);
+  return (size_t)p.max_splits * g.Cout * g.k * g.k * g.Cin * sizeof(float);
 }
 
 static void set_stats(IgemmArgs& a, const ConvStats* s, int slab0) {
@@ -1561,13 +1651,20 @@ dat_status conv_mfma_backward_weight(const bf16_t* x, const bf16_t* dy, float* d
   a.B = g.B; a.H = g.H; a.W = g.W; a.Cin = g.Cin; a.Ho = g.Ho; a.Wo = g.Wo; a.Cout = g.Cout;
   a.k = g.k; a.stride = g.stride; a.pad = g.pad;
   a.M = g.B * g.Ho * g.Wo; a.Ktot = g.k * g.k * g.Cin; a.pix_per_split = p.pix_per_split;
-  const dim3 grid((unsigned)p.gx, (unsigned)p.gy, (unsigned)p.splits);
+  a.splits = p.splits; a.gx = p.gx; a.gy = p.gy; a.chunk = p.chunk;
+  const int64_t work = (int64_t)p.gx * p.gy * p.splits;
+  if (work + 7 >= (1ll << 31)) return DAT_ERR_UNSUPPORTED;
+  const dim3 grid((unsigned)((work + 7) / 8 * 8));
   if (p.narrow) hipLaunchKernelGGL((wgrad_kernel<64, 128>), grid, dim3(kThreads), 0, st, a);
   else hipLaunchKernelGGL((wgrad_kernel<128, 128>), grid, dim3(kThreads), 0, st, a);
   DAT_LAUNCH_CHECK();
   const int64_t per_split = (int64_t)g.Cout * a.Ktot;
-  hipLaunchKernelGGL(wgrad_reduce_kernel, dim3((unsigned)((per_split + 31) / 32)), dim3(256), 0, st, (const float*)ws, p.splits,
-                     per_split, g.Cin, cin_real, scale, dw, absmax);
+  if (p.splits <= kFewSplits)
+    hipLaunchKernelGGL(wgrad_reduce_few_kernel, dim3((unsigned)((per_split + 1023) / 1024)), dim3(256), 0, st, (const float*)ws, p.splits,
+                       per_split, g.Cin, cin_real, scale, dw, absmax);
+  else
+    hipLaunchKernelGGL(wgrad_reduce_kernel, dim3((unsigned)((per_split + 31) / 32)), dim3(256), 0, st, (const float*)ws, p.splits,
+                       per_split, g.Cin, cin_real, scale, dw, absmax);
   DAT_LAUNCH_CHECK();
   return DAT_OK;
 }
@@ -1701,7 +1798,10 @@ extern "C" dat_status dat_conv_backward_weight_static(const uint16_t* x, const u
   ConvGeom g;
   if (!x || !dy || !dw || !geom_from(B, H, W, Cin, Cout, k, stride, pad, &g)) return DAT_ERR_ARG;
   if (!aligned(x, 16) || !aligned(dy, 16) || !aligned(dw, 16)) return DAT_ERR_ARG;
-  if (conv_mfma_wgrad_workspace(g) > (size_t)DAT_STATIC_SCRATCH_BYTES)
+  // (the limit counts one partial tile per chain of sums, which the pixel ranges of a call never outnumber by much)
+  const WgradPlan p = plan_wgrad(g);
+  const size_t tile_bytes = (size_t)Cout * k * k * Cin * sizeof(float), chains = ((size_t)B * g.Ho * g.Wo + p.chunk - 1) / p.chunk;
+  if (chains * tile_bytes > (size_t)DAT_STATIC_SCRATCH_BYTES || conv_mfma_wgrad_workspace(g) > (size_t)DAT_STATIC_SCRATCH_BYTES)
     return fail_with(DAT_ERR_UNSUPPORTED, "dat_conv_backward_weight_static: the split partial sums of this shape exceed the 32 MiB static scratch "
                                           "(use dat_conv_backward_weight)");
   void* ws = nullptr;

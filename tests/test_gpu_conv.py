@@ -175,3 +175,30 @@ def test_multi_stage_tiles_give_the_bits_of_the_single_stage_kernels(dat, shape)
     for a, b in zip(*res):
         assert torch.isfinite(a.float()).all() and a.float().abs().max() > 0
         assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+
+
+# pixel ranges of several chains of sums, few (<= 16) and many of them, both tile widths, images smaller than a tile
+WGRAD_SHAPES = [
+    (60, 14, 14, 256, 256, 3, 1, 1),   # 14 ranges of about 840 pixels, chains of 256
+    (60, 20, 20, 128, 136, 3, 1, 1),   # many ranges, ragged channel tile
+    (60, 28, 28, 64, 64, 3, 1, 1),     # narrow tiles, three workgroups per compute unit
+    (60, 28, 28, 128, 64, 1, 1, 0),    # narrow 1x1
+    (999, 3, 3, 256, 256, 3, 2, 1),    # 2x2 outputs: 16 images in a tile, ragged end
+    (700, 5, 5, 64, 200, 3, 1, 1),     # a tile ends inside an image of 25 pixels
+    (3, 65, 67, 40, 64, 5, 1, 2),      # rows longer than a tile, 5x5 window, channels that are no power of two
+]
+
+
+@pytest.mark.parametrize("shape", WGRAD_SHAPES)
+def test_backward_weight_sums_pixel_ranges(dat, shape):
+    """fp32 chains of n <= 320 terms plus the few partial sums: relative error about sqrt(n) 2^-24 = 1.1e-6."""
+    B, H, W, Ci, Co, k, st, pad = shape
+    g = torch.Generator(device="cuda").manual_seed(B + Co)
+    Ho, Wo = (H + 2 * pad - k) // st + 1, (W + 2 * pad - k) // st + 1
+    x, dy = (torch.randn(*s, device="cuda", generator=g).to(torch.bfloat16) for s in ((B, H, W, Ci), (B, Ho, Wo, Co)))
+    got = dat.conv_backward_weight(x, dy, k, st, pad).cpu().double()
+    xp, d64 = torch.nn.functional.pad(x.cpu().double(), (0, 0, pad, pad, pad, pad)), dy.cpu().double().view(-1, Co).t()
+    for r in range(k):
+        for s in range(k):
+            want = d64 @ xp[:, r:r + (Ho - 1) * st + 1:st, s:s + (Wo - 1) * st + 1:st].reshape(-1, Ci)
+            assert float((got[:, r, s] - want).norm() / want.norm()) < 1.1e-6, (r, s)
