@@ -108,6 +108,32 @@ struct IgemmArgs {
   const float* xf_tab;       // 4*Cin floats, layout of bn_input_grad's constants
 };
 
+// Several launches of one kernel as one grid: what differs between them.  The four parity classes of a stride-2
+// backward-data pass go this way, the classes with most taps first (their workgroups run longest).  Each class has
+// blocks [begin, next begin), a multiple of 8, so the tile numbering inside a class is that of a launch of its own.
+struct IgemmClass { const bf16_t* wt; int Hout, Wout, KH, KW, pad_h, pad_w, oh0, ow0, M, Ktot, stat_slab0, with_res, npt, begin; };
+struct IgemmClasses { int n; IgemmClass c[4]; };      // n = 0: an ordinary launch
+
+// Block number within its class, whose values replace those of `a`.
+__device__ __forceinline__ int enter_class(IgemmArgs& a, const IgemmClasses& cl, int bid) {
+  int begin = 0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {          // (constant indices: the arguments stay in scalar registers)
+    const IgemmClass& c = cl.c[i];
+    if (i < cl.n && bid >= c.begin) {
+      a.wt = c.wt; a.Hout = c.Hout; a.Wout = c.Wout; a.KH = c.KH; a.KW = c.KW; a.pad_h = c.pad_h; a.pad_w = c.pad_w;
+      a.oh0 = c.oh0; a.ow0 = c.ow0; a.M = c.M; a.Ktot = c.Ktot; a.stat_slab0 = c.stat_slab0; a.npt = c.npt;
+      begin = c.begin;
+    }
+  }
+  bool with_res = true;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    if (i < cl.n && bid >= cl.c[i].begin) with_res = cl.c[i].with_res != 0;
+  if (!with_res) a.res = nullptr;
+  return bid - begin;
+}
+
 __device__ __forceinline__ int64_t out_row(const IgemmArgs& a, int m) {
   if (a.ostep == 1 && a.outH == a.Hout && a.outW == a.Wout) return m;
   const int HW = a.Hout * a.Wout;
@@ -575,7 +601,7 @@ __device__ __forceinline__ void load_to_lds(BufRsrc r, unsigned char* dst, uint3
 }
 
 template <int TC, int TP, int WGC, int OCC, int BKT>
-__global__ __launch_bounds__(kThreads, OCC) void igemm_dma_kernel(IgemmArgs a) {
+__global__ __launch_bounds__(kThreads, OCC) void igemm_dma_kernel(IgemmArgs a, IgemmClasses cl) {
   constexpr int KS = BKT / 16, NS = BKT / 8;              // MFMA k-steps per tile; 16-byte slots per tile row
   constexpr int WGP = 4 / WGC;
   constexpr int WC = TC / WGC, WP = TP / WGP;
@@ -591,7 +617,8 @@ __global__ __launch_bounds__(kThreads, OCC) void igemm_dma_kernel(IgemmArgs a) {
   static_assert(TP % RPG == 0 && (BKT == 32 || BKT == 64), "tile rows must be whole load sweeps");
   __shared__ __attribute__((aligned(1024))) unsigned char lds[LDS_BYTES];
 
-  const int bid = blockIdx.x;
+  int bid = blockIdx.x;
+  if (cl.n) bid = enter_class(a, cl, bid);
   const int q = bid >> 3;
   const int ct = q % a.nct;
   const int pt = a.xcd_contiguous ? (bid & 7) * ((a.npt + 7) >> 3) + (q / a.nct) : (q / a.nct) * 8 + (bid & 7);
@@ -693,17 +720,29 @@ __global__ __launch_bounds__(kThreads, OCC) void igemm_dma_kernel(IgemmArgs a) {
   igemm_epilogue<TC, TP, WGC>(a, acc, lds, c0, m0, pt);
 }
 
+// Blocks of a launch in tiles of TP pixels; for a launch in classes also their block ranges.
+template <int TP>
+unsigned plan_blocks(IgemmArgs& a, IgemmClasses& cl) {
+  if (!cl.n) { a.npt = (a.M + TP - 1) / TP; return (unsigned)((a.npt + 7) / 8 * 8 * a.nct); }
+  int blocks = 0;
+  for (int i = 0; i < cl.n; ++i) {
+    cl.c[i].npt = (cl.c[i].M + TP - 1) / TP;
+    cl.c[i].begin = blocks;
+    blocks += (cl.c[i].npt + 7) / 8 * 8 * a.nct;
+  }
+  return (unsigned)blocks;
+}
+
 template <int TC, int TP, int WGC, int OCC, int BKT = 64>
-dat_status launch_igemm_dma(IgemmArgs a, hipStream_t st) {
+dat_status launch_igemm_dma(IgemmArgs a, hipStream_t st, IgemmClasses cl = IgemmClasses{}) {
   if ((int64_t)a.B * a.Hin * a.Win * a.Cin >= (1ll << 31) || (int64_t)a.Cout * a.Ktot >= (1ll << 31)) return DAT_ERR_UNSUPPORTED;
   if (a.Cin % BKT != 0 || a.Ktot < BKT || a.Ktot % BKT != 0) return DAT_ERR_UNSUPPORTED;
   if (a.xstride && (a.Cin != BKT || a.xstride % 8 != 0 || a.Cin % a.xstride != 0)) return DAT_ERR_UNSUPPORTED;   // one tap per k-tile
   a.nct = (a.Cout + TC - 1) / TC;
-  a.npt = (a.M + TP - 1) / TP;
-  if (a.npt == 0) return DAT_OK;
+  const unsigned blocks = plan_blocks<TP>(a, cl);
+  if (blocks == 0) return DAT_OK;
   a.xcd_contiguous = a.KH * a.KW > 1;   // filter windows: neighbouring tiles re-read each other's rows
-  const int npt8 = (a.npt + 7) / 8 * 8;
-  hipLaunchKernelGGL((igemm_dma_kernel<TC, TP, WGC, OCC, BKT>), dim3((unsigned)(npt8 * a.nct)), dim3(kThreads), 0, st, a);
+  hipLaunchKernelGGL((igemm_dma_kernel<TC, TP, WGC, OCC, BKT>), dim3(blocks), dim3(kThreads), 0, st, a, cl);
   DAT_LAUNCH_CHECK();
   return DAT_OK;
 }
@@ -725,7 +764,7 @@ dat_status launch_igemm_dma(IgemmArgs a, hipStream_t st) {
 // filter taps: every lane follows the tap and channel of its own 16-byte vector (a vector never straddles: Cin % 8
 // == 0), and the last tile is padded with zeros.
 template <int TC, int TP, int WGC, int S, int NT, int G, bool ANYC = false>
-__global__ __launch_bounds__(NT) void igemm_ring_kernel(IgemmArgs a) {
+__global__ __launch_bounds__(NT) void igemm_ring_kernel(IgemmArgs a, IgemmClasses cl) {
   constexpr int BKT = 64, KS = BKT / 16, NG = KS / G;       // MFMA k-steps per tile, in NG groups of G
   constexpr int WGP = NT / 64 / WGC;
   constexpr int WC = TC / WGC, WP = TP / WGP;
@@ -745,7 +784,8 @@ __global__ __launch_bounds__(NT) void igemm_ring_kernel(IgemmArgs a) {
   static_assert(LDS_BYTES <= 163840, "LDS of a CU");
   __shared__ __attribute__((aligned(1024))) unsigned char lds[LDS_BYTES];
 
-  const int bid = blockIdx.x;
+  int bid = blockIdx.x;
+  if (cl.n) bid = enter_class(a, cl, bid);
   const int q = bid >> 3;
   const int ct = q % a.nct;
   const int pt = a.xcd_contiguous ? (bid & 7) * ((a.npt + 7) >> 3) + (q / a.nct) : (q / a.nct) * 8 + (bid & 7);
@@ -903,16 +943,15 @@ __global__ __launch_bounds__(NT) void igemm_ring_kernel(IgemmArgs a) {
 }
 
 template <int TC, int TP, int WGC, int S, int NT, int G, bool ANYC = false>
-dat_status launch_igemm_ring(IgemmArgs a, hipStream_t st) {
+dat_status launch_igemm_ring(IgemmArgs a, hipStream_t st, IgemmClasses cl = IgemmClasses{}) {
   if ((int64_t)a.B * a.Hin * a.Win * a.Cin >= (1ll << 31) || (int64_t)a.Cout * a.Ktot >= (1ll << 31)) return DAT_ERR_UNSUPPORTED;
   if (a.Ktot < 64 || a.xf_tab || a.xstride) return DAT_ERR_UNSUPPORTED;
   if (ANYC ? (a.Cin % 8 != 0 || a.Ktot != a.KH * a.KW * a.Cin) : a.Cin % 64 != 0) return DAT_ERR_UNSUPPORTED;
   a.nct = (a.Cout + TC - 1) / TC;
-  a.npt = (a.M + TP - 1) / TP;
-  if (a.npt == 0) return DAT_OK;
+  const unsigned blocks = plan_blocks<TP>(a, cl);
+  if (blocks == 0) return DAT_OK;
   a.xcd_contiguous = 0;
-  const int npt8 = (a.npt + 7) / 8 * 8;
-  hipLaunchKernelGGL((igemm_ring_kernel<TC, TP, WGC, S, NT, G, ANYC>), dim3((unsigned)(npt8 * a.nct)), dim3(NT), 0, st, a);
+  hipLaunchKernelGGL((igemm_ring_kernel<TC, TP, WGC, S, NT, G, ANYC>), dim3(blocks), dim3(NT), 0, st, a, cl);
   DAT_LAUNCH_CHECK();
   return DAT_OK;
 }
@@ -1081,6 +1120,32 @@ dat_status run_igemm(const IgemmArgs& a, hipStream_t st) {
     return pick_depth<64, 128, 2>(a, st);
   }
   return pick_depth_wide(a, st);
+}
+
+// The classes of one backward-data pass as one launch, if a kernel takes them that way (*done); `a` carries the values of
+// the class with most taps.  128-pixel tiles; the rules are those of pick_ring and run_igemm for the sum of the tiles.
+dat_status run_igemm_classes(const IgemmArgs& a, const IgemmClasses& cl, hipStream_t st, bool* done) {
+  *done = false;
+  const bool tile160 = a.Cout % 160 == 0 && g_tile160.load(std::memory_order_relaxed), any = a.Cin % 64 != 0;
+  if (any && !(tile160 && a.Ktot >= 512)) return DAT_OK;
+  if (a.Ktot < 64 || a.Cin % 8 != 0 || a.Cout % 8 != 0 || a.xf_tab || a.xstride || (a.stat_mode == 3 && a.Cout <= 64)) return DAT_OK;
+  *done = true;
+  g_launches.fetch_add(1, std::memory_order_relaxed);
+  int64_t tiles = 0;
+  for (int i = 0; i < cl.n; ++i) tiles += (cl.c[i].M + 127) / 128;
+  const int64_t cus = compute_units(), t = tiles * ((a.Cout + 127) / 128);
+  if (any) return launch_igemm_ring<160, 128, 1, 2, 256, 1, true>(a, st, cl);
+  if (tile160 && (a.Cout % 128 != 0 || 2 * tiles * (a.Cout / 160) > cus)) return launch_igemm_ring<160, 128, 1, 2, 256, 1>(a, st, cl);
+  const bool narrow = g_narrow_underfilled.load(std::memory_order_relaxed);
+  if (narrow && a.Cout > 64 && t <= cus) {
+    if (2 * t > cus) return launch_igemm_ring<128, 128, 2, 4, 512, 4>(a, st, cl);
+    if (4 * t > cus) return launch_igemm_ring<64, 128, 2, 3, 256, 4>(a, st, cl);
+    return launch_igemm_ring<32, 128, 1, 4, 256, 4>(a, st, cl);
+  }
+  if (narrow && a.Cout <= 64 && 2 * tiles <= cus) return launch_igemm_ring<32, 128, 1, 4, 256, 4>(a, st, cl);
+  if (a.Cout <= 32) return launch_igemm_dma<32, 128, 1, 6>(a, st, cl);
+  if (a.Cout <= 64) return launch_igemm_dma<64, 128, 2, 5>(a, st, cl);
+  return launch_igemm_dma<128, 128, 2, 4>(a, st, cl);
 }
 
 // ---- weight layouts ---------------------------------------------------------------------------
@@ -1573,24 +1638,54 @@ dat_status conv_mfma_backward_data(const bf16_t* dy, const bf16_t* wT, bf16_t* d
     return run_igemm(a, st);
   }
   if (g.stride != 2) return DAT_ERR_UNSUPPORTED;
+  a.ostep = 2;
+  set_stats(a, stats, 0);
+  const bf16_t* const stored = a.res;
+  IgemmClass cls[4];
+  int n = 0, slab0 = 0;
   int64_t base = 0;
-  int slab0 = 0;
   for (int q = 0; q < 4; ++q) {
     const int ph = q >> 1, pw = q & 1;
     const ParityClass ch = parity_class(ph, g.k, g.pad), cw = parity_class(pw, g.k, g.pad);
-    a.wt = wT + base * g.Cin * g.Cout;
-    a.Hout = (g.H - ph + 1) / 2; a.Wout = (g.W - pw + 1) / 2;
-    a.KH = ch.nr; a.KW = cw.nr; a.pad_h = ch.pad; a.pad_w = cw.pad;
-    a.ostep = 2; a.oh0 = ph; a.ow0 = pw;
-    a.M = g.B * a.Hout * a.Wout; a.Ktot = ch.nr * cw.nr * g.Cout;
-    const bool taps = a.Ktot != 0;
-    if (!taps) a.KH = a.KW = 1;         // class without taps: the launch only writes zeros (or keeps the stored gradient)
-    if (sparse == 2) a.res = q == 0 ? dx : nullptr;   // the stored gradient exists at even rows and columns only
-    set_stats(a, stats, slab0);
+    IgemmClass c;
+    c.wt = wT + base * g.Cin * g.Cout;
+    c.Hout = (g.H - ph + 1) / 2; c.Wout = (g.W - pw + 1) / 2;
+    c.KH = ch.nr; c.KW = cw.nr; c.pad_h = ch.pad; c.pad_w = cw.pad;
+    c.oh0 = ph; c.ow0 = pw;
+    c.M = g.B * c.Hout * c.Wout; c.Ktot = ch.nr * cw.nr * g.Cout;
+    c.with_res = !(sparse == 2 && q != 0);            // the stored gradient exists at even rows and columns only
+    c.stat_slab0 = slab0; c.npt = c.begin = 0;
+    const bool taps = c.Ktot != 0;
+    if (!taps) c.KH = c.KW = 1;         // class without taps: only writes zeros (or keeps the stored gradient)
     if (sparse == 1 && !taps) continue;               // left unwritten: the accumulating pass that follows skips them
-    if (a.M > 0) { dat_status s = run_igemm(a, st); if (s != DAT_OK) return s; }
-    slab0 += (a.M + kPixelTile - 1) / kPixelTile;
+    if (c.M > 0) cls[n++] = c;
+    slab0 += (c.M + kPixelTile - 1) / kPixelTile;
     base += (int64_t)ch.nr * cw.nr;
+  }
+  auto take = [&](const IgemmClass& c) {
+    a.wt = c.wt; a.Hout = c.Hout; a.Wout = c.Wout; a.KH = c.KH; a.KW = c.KW; a.pad_h = c.pad_h; a.pad_w = c.pad_w;
+    a.oh0 = c.oh0; a.ow0 = c.ow0; a.M = c.M; a.Ktot = c.Ktot; a.stat_slab0 = c.stat_slab0;
+    a.res = c.with_res ? stored : nullptr;
+  };
+  if (n > 1) {
+    // one launch: at 13 images of 32x32 four launches of a few workgroups each take about 8 us apiece, and in the larger
+    // layers every class had a last wave of its own (attack on the
+    // pre-activation ResNet-18, 13 images: 9.2 -> 8.4 ms; CIFAR ResNet-18, 512 images: 29.0 -> 27.6; WRN-34-10: 97.6 -> 95.8)
+    IgemmClasses cl{};
+    cl.n = n;
+    for (int i = 0; i < n; ++i) cl.c[i] = cls[i];
+    for (int i = 1; i < n; ++i)          // most taps first
+      for (int j = i; j > 0 && cl.c[j].Ktot > cl.c[j - 1].Ktot; --j) { const IgemmClass t = cl.c[j]; cl.c[j] = cl.c[j - 1]; cl.c[j - 1] = t; }
+    take(cl.c[0]);
+    a.res = stored;
+    bool done;
+    const dat_status s = run_igemm_classes(a, cl, st, &done);
+    if (done) { if (stats) stats->nslabs = slab0; return s; }
+  }
+  for (int i = 0; i < n; ++i) {
+    take(cls[i]);
+    const dat_status s = run_igemm(a, st);
+    if (s != DAT_OK) return s;
   }
   if (stats) stats->nslabs = slab0;
   return DAT_OK;
