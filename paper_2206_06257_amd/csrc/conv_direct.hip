@@ -9,7 +9,8 @@
 // weights at a stride of k*k*Cin floats took 18 / 68 us (forward), 37 / 27 us (backward-data); a wavefront per weight
 // walking all pixels 310 / 235 us (backward-weight): the tiles make every global access contiguous and share it
 // between the threads of a workgroup, and the pixel range of backward-weight is split over several hundred workgroups.
-// The whole iteration of that configuration (FGSM, gradient, update, quantizer): 993 -> 364 us.
+// The whole iteration of that configuration (FGSM, gradient, update, quantizer): 993 -> 364 us, and 253 us since the strided
+// layer's backward-data pass walks only the taps a pixel sees (48 -> 18 us) and the layers around it were split further.
 #include "kernels.h"
 
 namespace dat {
@@ -20,20 +21,31 @@ constexpr int KC = 32;        // depth of a staged chunk
 // One output tile of  D[m][n] = sum_k A(m, k) B(k, n):  TM x TN outputs per workgroup, MM x MN per thread.
 //   forward (DATA = false):       m = output pixel, n = output channel, k = (r, s, input channel)
 //   backward-data (DATA = true):  m = input pixel,  n = input channel,  k = (r, s, output channel)
+// A strided layer's input pixels fall into stride^2 classes by the remainder of their row and column, and a pixel sees
+// only the taps of its class (a quarter of them at stride 2): blockIdx.z is the class, k runs over its taps.
+// A thread's two rows or columns are neighbours, one 8-byte LDS read.  (fp64 in LDS saves the conversions and costs as much
+// in LDS bandwidth: no faster.)
 template <int TM, int TN, int MM, int MN, bool DATA>
 __global__ __launch_bounds__(kT) void direct_tile_kernel(const float* __restrict__ a, const float* __restrict__ w, const float* __restrict__ res,
                                                          float* __restrict__ d, ConvGeom g) {
   static_assert((TM / MM) * (TN / MN) == kT, "one output block per thread");
   constexpr int LA = TM * KC / kT, LB = (TN * KC + kT - 1) / kT;    // elements per thread and chunk
-  constexpr int NT = TN / MN, MT = TM / MM;
-  __shared__ float As[KC][TM + 1], Bs[KC][TN + 1];
+  constexpr int NT = TN / MN;
+  __shared__ __attribute__((aligned(16))) float As[KC][TM + 2], Bs[KC][TN + 2];
   const int tid = threadIdx.x;
   const int Hm = DATA ? g.H : g.Ho, Wm = DATA ? g.W : g.Wo;         // grid of the result's pixels
   const int Ha = DATA ? g.Ho : g.H, Wa = DATA ? g.Wo : g.W;         // ... of the gathered operand's
   const int N = DATA ? g.Cin : g.Cout, Ca = DATA ? g.Cout : g.Cin;
-  const int K = g.k * g.k * Ca;
-  const int64_t M = (int64_t)g.B * Hm * Wm;
+  // this workgroup's pixels: rows ph, ph + S, ... and columns pw, pw + S, ...; its taps: rf, rf + S, ... and sf, sf + S, ...
+  const int S = DATA ? g.stride : 1;
+  const int ph = DATA ? (int)blockIdx.z / S : 0, pw = DATA ? (int)blockIdx.z % S : 0;
+  const int rf = DATA ? (ph + g.pad) % S : 0, sf = DATA ? (pw + g.pad) % S : 0;
+  const int nr = rf < g.k ? (g.k - rf + S - 1) / S : 0, ns = sf < g.k ? (g.k - sf + S - 1) / S : 0;
+  const int Hc = (Hm - ph + S - 1) / S, Wc = (Wm - pw + S - 1) / S;
+  const int K = nr * ns * Ca, nsd = ns > 0 ? ns : 1;
+  const int64_t M = (int64_t)g.B * Hc * Wc;
   const int64_t m0 = (int64_t)blockIdx.x * TM;
+  if (m0 >= M) return;
   const int n0 = blockIdx.y * TN;
 
   // operand loads: consecutive threads walk consecutive k (consecutive channels of one tap)
@@ -44,10 +56,10 @@ __global__ __launch_bounds__(kT) void direct_tile_kernel(const float* __restrict
     const int64_t m = m0 + lrow + (kT / KC) * i;
     mv[i] = m < M;
     const int64_t mm = mv[i] ? m : 0;
-    const int64_t n = mm / ((int64_t)Hm * Wm); const int rem = (int)(mm - n * Hm * Wm);
-    const int h = rem / Wm, x = rem - h * Wm;
-    hb[i] = DATA ? h + g.pad : h * g.stride - g.pad;
-    wb[i] = DATA ? x + g.pad : x * g.stride - g.pad;
+    const int64_t n = mm / ((int64_t)Hc * Wc); const int rem = (int)(mm - n * Hc * Wc);
+    const int h = rem / Wc, x = rem - h * Wc;
+    hb[i] = DATA ? (h * S + ph + g.pad - rf) / S : h * g.stride - g.pad;
+    wb[i] = DATA ? (x * S + pw + g.pad - sf) / S : x * g.stride - g.pad;
     nb[i] = n * Ha * Wa;
   }
   float ra[LA], rb[LB];
@@ -55,16 +67,11 @@ __global__ __launch_bounds__(kT) void direct_tile_kernel(const float* __restrict
     const int k = k0 + kk;
     const bool kv = k < K;
     const int tap = (kv ? k : 0) / Ca, c = (kv ? k : 0) - tap * Ca;
-    const int r = tap / g.k, s = tap - r * g.k;
+    const int r = tap / nsd, s = tap - r * nsd;
 #pragma unroll
     for (int i = 0; i < LA; ++i) {
-      int h = DATA ? hb[i] - r : hb[i] + r, x = DATA ? wb[i] - s : wb[i] + s;
-      bool ok = kv && mv[i] && h >= 0 && x >= 0;
-      if (DATA && g.stride != 1) {
-        ok = ok && h % g.stride == 0 && x % g.stride == 0;
-        h /= g.stride; x /= g.stride;
-      }
-      ok = ok && h < Ha && x < Wa;
+      const int h = DATA ? hb[i] - r : hb[i] + r, x = DATA ? wb[i] - s : wb[i] + s;
+      const bool ok = kv && mv[i] && h >= 0 && x >= 0 && h < Ha && x < Wa;
       ra[i] = ok ? a[(nb[i] + (int64_t)h * Wa + x) * Ca + c] : 0.f;
     }
 #pragma unroll
@@ -73,8 +80,8 @@ __global__ __launch_bounds__(kT) void direct_tile_kernel(const float* __restrict
       if (DATA) {        // w[co][r][s][ci]: ci (= n) is contiguous
         const int n = idx % TN, kb = idx / TN, k2 = k0 + kb;
         const bool ok = kb < KC && k2 < K && n0 + n < N;
-        const int tap2 = (ok ? k2 : 0) / Ca, co = (ok ? k2 : 0) - tap2 * Ca;
-        rb[i] = ok ? w[((int64_t)co * g.k * g.k + tap2) * N + n0 + n] : 0.f;
+        const int t2 = (ok ? k2 : 0) / Ca, co = (ok ? k2 : 0) - t2 * Ca, r2 = t2 / nsd, s2 = t2 - r2 * nsd;
+        rb[i] = ok ? w[((int64_t)(co * g.k + rf + r2 * S) * g.k + sf + s2 * S) * N + n0 + n] : 0.f;
       } else {           // w[co][k]: k is contiguous
         const int n = idx / KC;
         rb[i] = (n < TN && n0 + n < N && kv) ? w[(int64_t)(n0 + n) * K + k] : 0.f;
@@ -105,10 +112,10 @@ __global__ __launch_bounds__(kT) void direct_tile_kernel(const float* __restrict
 #pragma unroll 8
     for (int k = 0; k < KC; ++k) {
       double av[MM], bv[MN];
-#pragma unroll
-      for (int i = 0; i < MM; ++i) av[i] = (double)As[k][tm + MT * i];
-#pragma unroll
-      for (int j = 0; j < MN; ++j) bv[j] = (double)Bs[k][tn + NT * j];
+      if (MM == 2) { const float2 v = *reinterpret_cast<const float2*>(&As[k][tm * 2]); av[0] = (double)v.x; av[MM - 1] = (double)v.y; }
+      else av[0] = (double)As[k][tm];
+      if (MN == 2) { const float2 v = *reinterpret_cast<const float2*>(&Bs[k][tn * 2]); bv[0] = (double)v.x; bv[MN - 1] = (double)v.y; }
+      else bv[0] = (double)Bs[k][tn];
 #pragma unroll
       for (int i = 0; i < MM; ++i)
 #pragma unroll
@@ -118,25 +125,31 @@ __global__ __launch_bounds__(kT) void direct_tile_kernel(const float* __restrict
   }
 #pragma unroll
   for (int i = 0; i < MM; ++i) {
-    const int64_t m = m0 + tm + MT * i;
+    const int64_t m = m0 + tm * MM + i;
     if (m >= M) continue;
+    int64_t pix = m;
+    if (DATA && S != 1) {
+      const int64_t n = m / ((int64_t)Hc * Wc); const int rem = (int)(m - n * Hc * Wc), h = rem / Wc;
+      pix = (n * Hm + h * S + ph) * Wm + (rem - h * Wc) * S + pw;
+    }
 #pragma unroll
     for (int j = 0; j < MN; ++j) {
-      const int n = n0 + tn + NT * j;
+      const int n = n0 + tn * MN + j;
       if (n >= N) continue;
       double v = acc[i][j];
-      if (res) v += (double)res[m * N + n];
-      d[m * N + n] = (float)v;
+      if (res) v += (double)res[pix * N + n];
+      d[pix * N + n] = (float)v;
     }
   }
 }
 
 template <bool DATA>
 dat_status launch_direct(const float* a, const float* w, const float* res, float* d, const ConvGeom& g, hipStream_t st) {
-  const int64_t M = (int64_t)g.B * (DATA ? g.H * g.W : g.Ho * g.Wo);
+  const int S = DATA ? g.stride : 1;                     // (the class of the first row and column is the largest)
+  const int64_t M = (int64_t)g.B * (DATA ? ((g.H + S - 1) / S) * ((g.W + S - 1) / S) : g.Ho * g.Wo);
   const int N = DATA ? g.Cin : g.Cout;
   // narrow results (the 3-channel input gradient, the first layers' widths) in narrow tiles: no idle columns
-#define DAT_DIRECT(TM, TN, MM, MN) hipLaunchKernelGGL((direct_tile_kernel<TM, TN, MM, MN, DATA>), dim3((unsigned)((M + TM - 1) / TM), (unsigned)((N + TN - 1) / TN)), dim3(kT), 0, st, a, w, res, d, g)
+#define DAT_DIRECT(TM, TN, MM, MN) hipLaunchKernelGGL((direct_tile_kernel<TM, TN, MM, MN, DATA>), dim3((unsigned)((M + TM - 1) / TM), (unsigned)((N + TN - 1) / TN), (unsigned)(S * S)), dim3(kT), 0, st, a, w, res, d, g)
   if (N <= 4) DAT_DIRECT(128, 4, 2, 1);
   else if (N <= 16) DAT_DIRECT(64, 16, 2, 2);
   else DAT_DIRECT(32, 32, 2, 2);
@@ -150,7 +163,7 @@ dat_status launch_direct(const float* a, const float* w, const float* res, float
 // direct_wgrad_reduce_kernel adds the splits in order.
 __global__ __launch_bounds__(kT) void direct_wgrad_kernel(const float* __restrict__ x, const float* __restrict__ dy, double* __restrict__ ws,
                                                           ConvGeom g, int64_t pps) {
-  __shared__ float As[KC][33], Bs[KC][33];        // dY[pixel][co], X[pixel][j]
+  __shared__ __attribute__((aligned(16))) float As[KC][34], Bs[KC][34];        // dY[pixel][co], X[pixel][j]
   const int tid = threadIdx.x;
   const int J = g.k * g.k * g.Cin;
   const int c0 = blockIdx.x * 32, j0 = blockIdx.y * 32;
@@ -182,9 +195,10 @@ __global__ __launch_bounds__(kT) void direct_wgrad_kernel(const float* __restric
     if (pb + KC < p1) fetch(pb + KC);
 #pragma unroll 8
     for (int k = 0; k < KC; ++k) {
-      const double a0 = (double)As[k][tm], a1 = (double)As[k][tm + 16], b0 = (double)Bs[k][tn], b1 = (double)Bs[k][tn + 16];
-      acc[0][0] = __builtin_fma(a0, b0, acc[0][0]); acc[0][1] = __builtin_fma(a0, b1, acc[0][1]);
-      acc[1][0] = __builtin_fma(a1, b0, acc[1][0]); acc[1][1] = __builtin_fma(a1, b1, acc[1][1]);
+      const float2 af = *reinterpret_cast<const float2*>(&As[k][tm * 2]), bf = *reinterpret_cast<const float2*>(&Bs[k][tn * 2]);
+      const double2 av = make_double2((double)af.x, (double)af.y), bv = make_double2((double)bf.x, (double)bf.y);
+      acc[0][0] = __builtin_fma(av.x, bv.x, acc[0][0]); acc[0][1] = __builtin_fma(av.x, bv.y, acc[0][1]);
+      acc[1][0] = __builtin_fma(av.y, bv.x, acc[1][0]); acc[1][1] = __builtin_fma(av.y, bv.y, acc[1][1]);
     }
     __syncthreads();
   }
@@ -193,7 +207,7 @@ __global__ __launch_bounds__(kT) void direct_wgrad_kernel(const float* __restric
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
-      const int co = c0 + tm + 16 * i, jj = j0 + tn + 16 * q;
+      const int co = c0 + tm * 2 + i, jj = j0 + tn * 2 + q;
       if (co < g.Cout && jj < J) dst[(int64_t)co * J + jj] = acc[i][q];
     }
 }

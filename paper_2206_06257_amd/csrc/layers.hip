@@ -379,14 +379,15 @@ __global__ __launch_bounds__(kT) void colreduce_kernel(const T* __restrict__ x, 
 #pragma unroll
   for (int j = 0; j < 8; ++j) { red[0][tid][j] = a1[j]; red[1][tid][j] = a2[j]; }
   __syncthreads();
-  if (rr == 0) {
-    for (int q = 1; q < rpp; ++q) {
-#pragma unroll
-      for (int j = 0; j < 8; ++j) { a1[j] += red[0][q * tpr + cv][j]; a2[j] += red[1][q * tpr + cv][j]; }
-    }
-    float* p = partial + (int64_t)blockIdx.x * 2 * C;
-    V8<float>::store(p + c0, a1);
-    V8<float>::store(p + C + c0, a2);
+  // one thread per sum and channel adds the row groups in order (as eight channels per thread the chain of dependent LDS
+  // reads was most of the launch for narrow tensors: 16 channels of 32x32, 32 images 12 us)
+  for (int q = tid; q < 2 * C; q += kT) {
+    const int which = q >= C, c = which ? q - C : q;
+    const float* col = &red[which][c >> 3][c & 7];
+    float t = col[0];
+#pragma unroll 8
+    for (int g = 1; g < rpp; ++g) t += col[(int64_t)g * tpr * 8];
+    partial[(int64_t)blockIdx.x * 2 * C + q] = t;
   }
 }
 
@@ -826,6 +827,42 @@ __global__ __launch_bounds__(kT) void gap_fwd_kernel(const T* __restrict__ x, fl
 #pragma unroll
   for (int j = 0; j < 8; ++j) s[j] *= inv;
   V8<float>::store(pooled + (int64_t)n * C + cv * 8, s);
+}
+
+// The same for larger maps (more than 64 pixels), where a thread per vector is a long chain on few workgroups (32 channels
+// of 16x16, 32 images: one workgroup, 21 us): 32 threads share a vector, thread g adds the pixels g, g + 32, ..., then
+// the 32 sums are added in order.
+template <typename T>
+__global__ __launch_bounds__(kT) void gap_fwd_wide_kernel(const T* __restrict__ x, float* __restrict__ pooled, int B, int HW, int C) {
+  __shared__ float red[kT][9];                     // (9: the eight channels of the 8 vectors' sums fall on different banks)
+  const int tpr = C / 8, vl = threadIdx.x & 7, grp = threadIdx.x >> 3;
+  const int64_t v = (int64_t)blockIdx.x * 8 + vl;
+  const bool live = v < (int64_t)B * tpr;
+  const int cv = live ? (int)(v % tpr) : 0, n = live ? (int)(v / tpr) : 0;
+  const T* base = x + (int64_t)n * HW * C + cv * 8;
+  float s[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) s[j] = 0.f;
+  if (live) {
+#pragma unroll 4
+    for (int i = grp; i < HW; i += 32) {
+      float xv[8];
+      V8<T>::load(base + (int64_t)i * C, xv);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) s[j] += xv[j];
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < 8; ++j) red[threadIdx.x][j] = s[j];
+  __syncthreads();
+  if (threadIdx.x >= 64) return;
+  const int ov = threadIdx.x >> 3, oc = threadIdx.x & 7;
+  const int64_t vo = (int64_t)blockIdx.x * 8 + ov;
+  if (vo >= (int64_t)B * tpr) return;
+  float t = 0.f;
+#pragma unroll
+  for (int g = 0; g < 32; ++g) t += red[g * 8 + ov][oc];
+  pooled[vo * 8 + oc] = t * (1.0f / (float)HW);    // vector vo = image * (C/8) + channel vector
 }
 
 template <typename T>
@@ -1297,6 +1334,13 @@ dat_status maxpool_backward(const uint8_t* arg, const void* dout, void* dx, bool
 
 dat_status gap_forward(const void* x, float* pooled, int dtype, int B, int HW, int C, hipStream_t st) {
   const int64_t nvec = (int64_t)B * (C / 8);
+  if (HW > 64) {
+    DAT_BY_DTYPE(dtype,
+      hipLaunchKernelGGL(gap_fwd_wide_kernel<float>, dim3((unsigned)((nvec + 7) / 8)), dim3(kT), 0, st, (const float*)x, pooled, B, HW, C),
+      hipLaunchKernelGGL(gap_fwd_wide_kernel<bf16_t>, dim3((unsigned)((nvec + 7) / 8)), dim3(kT), 0, st, (const bf16_t*)x, pooled, B, HW, C));
+    DAT_LAUNCH_CHECK();
+    return DAT_OK;
+  }
   DAT_BY_DTYPE(dtype,
     hipLaunchKernelGGL(gap_fwd_kernel<float>, dim3(nblk(nvec)), dim3(kT), 0, st, (const float*)x, pooled, B, HW, C),
     hipLaunchKernelGGL(gap_fwd_kernel<bf16_t>, dim3(nblk(nvec)), dim3(kT), 0, st, (const bf16_t*)x, pooled, B, HW, C));

@@ -14,6 +14,7 @@ pytestmark = pytest.mark.gpu
     (0, 1, 2, 2),        # one pixel left after the strided layer; result tiles almost empty
     (0, 3, 17, 13),      # odd sizes: the strided layer's input gradient has rows without taps, pixel tails in every tile
     (0, 33, 8, 9),       # several pixel ranges in backward-weight, the last one short
+    (0, 5, 33, 21),      # a pooled map of more than 64 pixels (17 x 11): 32 threads share a vector
     (100, 2, 18, 14),    # 1x1, 3x3, strided projections, channel counts 8 .. 32
 ])
 def test_fp32_model_off_tile_sizes(arch, B, H, W):
