@@ -19,9 +19,9 @@ __device__ __forceinline__ PhiloxWords philox_block(uint64_t blk, uint64_t seed,
     const uint64_t p1 = (uint64_t)0xCD9E8D57u * (uint64_t)c2;
     const uint32_t hi0 = (uint32_t)(p0 >> 32), lo0 = (uint32_t)p0;
     const uint32_t hi1 = (uint32_t)(p1 >> 32), lo1 = (uint32_t)p1;
-    c0 = hi1 ^ c1 ^ ka;
+    c0 = __builtin_amdgcn_bitop3_b32(hi1, c1, ka, 0x96);      // three-way xor, one instruction
     c1 = lo1;
-    c2 = hi0 ^ c3 ^ kb;
+    c2 = __builtin_amdgcn_bitop3_b32(hi0, c3, kb, 0x96);
     c3 = lo0;
     ka += 0x9E3779B9u;
     kb += 0xBB67AE85u;
