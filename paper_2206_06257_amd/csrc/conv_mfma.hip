@@ -787,8 +787,7 @@ __global__ __launch_bounds__(NT) void igemm_ring_kernel(IgemmArgs a, IgemmClasse
   int bid = blockIdx.x;
   if (cl.n) bid = enter_class(a, cl, bid);
   const int q = bid >> 3;
-  const int ct = q % a.nct;
-  const int pt = a.xcd_contiguous ? (bid & 7) * ((a.npt + 7) >> 3) + (q / a.nct) : (q / a.nct) * 8 + (bid & 7);
+  const int ct = q % a.nct, pt = (q / a.nct) * 8 + (bid & 7);
   if (pt >= a.npt) return;
   const int c0 = ct * TC, m0 = pt * TP;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -950,7 +949,6 @@ dat_status launch_igemm_ring(IgemmArgs a, hipStream_t st, IgemmClasses cl = Igem
   a.nct = (a.Cout + TC - 1) / TC;
   const unsigned blocks = plan_blocks<TP>(a, cl);
   if (blocks == 0) return DAT_OK;
-  a.xcd_contiguous = 0;
   hipLaunchKernelGGL((igemm_ring_kernel<TC, TP, WGC, S, NT, G, ANYC>), dim3(blocks), dim3(NT), 0, st, a, cl);
   DAT_LAUNCH_CHECK();
   return DAT_OK;
@@ -1066,6 +1064,10 @@ RingPick pick_ring(const IgemmArgs& a) {
     if (t128 <= cus && 2 * t128 >= cus) return kR256x128;
   }
   if (!g_narrow_underfilled.load(std::memory_order_relaxed)) return kRNone;
+  // A backward-data pass that igemm_kernel may also run with its operand transform (conv_mfma_bn_operand_ok) leaves its
+  // batch-norm sums in the same order either way: 64-channel tiles of 256 threads, or the 128-channel single-stage kernel.
+  if (a.stat_mode >= 2 && a.KH * a.KW == 1 && a.ostep == 1 && a.Cout > 32 && a.Cout <= 128 && a.Cin >= 2 * a.Cout)
+    return a.Cout <= 64 && 2 * p128 <= cus ? kR64 : kRNone;
   const int64_t t = p128 * ((a.Cout + 127) / 128);
   if (a.Cout > 64 && t <= cus) return 2 * t > cus ? kR128 : 4 * t > cus ? kR64 : kR32;
   if (a.Cout <= 64 && 2 * p128 <= cus) return kR32;
@@ -1583,7 +1585,7 @@ static void set_stats(IgemmArgs& a, const ConvStats* s, int slab0) {
 
 int64_t conv_mfma_launch_count() { return g_launches.load(std::memory_order_relaxed); }
 
-constexpr int kPixelTile = 128;   // TP of every configuration run_igemm selects
+constexpr int kPixelTile = 128;   // smallest TP of the configurations run_igemm selects (pixel_tile gives the one of a launch)
 
 int conv_stat_slabs(int64_t rows, int stride) {
   // stride 2 backward-data runs four launches over the parity classes: at most 3 extra partial tiles
