@@ -2,14 +2,17 @@
 // runs of the ResNets that cross-check the bf16 MFMA path).  The three contractions run as tiled products on the vector
 // units: a workgroup stages a k-chunk of both operands in LDS (the im2col gather happens on the way in, the next chunk
 // is in registers meanwhile) and every thread keeps a small block of fp64 sums.  The sum of an output runs over
-// (filter row, filter column, channel) in that order, padding adding exact zeros.
+// (filter row, filter column, channel) in that order.  A tap outside the image is no term of the sum.  It is staged as a
+// zero, which adds nothing as long as the other factor is finite; a workgroup that meets an infinity or a NaN in that
+// factor (the weights; the output gradient in backward-weight) tests every tap from there on instead, so that border pixels
+// and weights that never see the value stay finite.
 //
 // What bounds them: at the toy configuration's sizes (32 images of 32x32, 3 -> 16 -> 32 channels) each launch is a
 // single round of workgroups and its time is the latency of K/32 chunks.  One thread per output element reading the
 // weights at a stride of k*k*Cin floats took 18 / 68 us (forward), 37 / 27 us (backward-data); a wavefront per weight
 // walking all pixels 310 / 235 us (backward-weight): the tiles make every global access contiguous and share it
 // between the threads of a workgroup, and the pixel range of backward-weight is split over several hundred workgroups.
-// The whole iteration of that configuration (FGSM, gradient, update, quantizer): 993 -> 364 us, and 253 us since the strided
+// The whole iteration of that configuration (FGSM, gradient, update, quantizer): 993 -> 364 us, and 257 us since the strided
 // layer's backward-data pass walks only the taps a pixel sees (48 -> 18 us) and the layers around it were split further.
 #include "kernels.h"
 
@@ -17,6 +20,8 @@ namespace dat {
 namespace {
 constexpr int kT = 256;
 constexpr int KC = 32;        // depth of a staged chunk
+
+__device__ __forceinline__ bool not_finite(float v) { return (__float_as_uint(v) & 0x7f800000u) == 0x7f800000u; }
 
 // One output tile of  D[m][n] = sum_k A(m, k) B(k, n):  TM x TN outputs per workgroup, MM x MN per thread.
 //   forward (DATA = false):       m = output pixel, n = output channel, k = (r, s, input channel)
@@ -32,6 +37,7 @@ __global__ __launch_bounds__(kT) void direct_tile_kernel(const float* __restrict
   constexpr int LA = TM * KC / kT, LB = (TN * KC + kT - 1) / kT;    // elements per thread and chunk
   constexpr int NT = TN / MN;
   __shared__ __attribute__((aligned(16))) float As[KC][TM + 2], Bs[KC][TN + 2];
+  __shared__ int test_taps;            // a weight that is not finite has been staged
   const int tid = threadIdx.x;
   const int Hm = DATA ? g.H : g.Ho, Wm = DATA ? g.W : g.Wo;         // grid of the result's pixels
   const int Ha = DATA ? g.Ho : g.H, Wa = DATA ? g.Wo : g.W;         // ... of the gathered operand's
@@ -95,6 +101,7 @@ __global__ __launch_bounds__(kT) void direct_tile_kernel(const float* __restrict
     for (int i = 0; i < LB; ++i) {
       const int idx = tid + kT * i;
       if (TN * KC % kT != 0 && idx >= TN * KC) continue;
+      if (not_finite(rb[i])) test_taps = 1;
       if (DATA) Bs[idx / TN][idx % TN] = rb[i]; else Bs[kk][idx / KC] = rb[i];
     }
   };
@@ -104,11 +111,39 @@ __global__ __launch_bounds__(kT) void direct_tile_kernel(const float* __restrict
   for (int i = 0; i < MM; ++i)
 #pragma unroll
     for (int j = 0; j < MN; ++j) acc[i][j] = 0.0;
+  // one chunk, leaving out the taps that lie outside the image
+  auto tested_chunk = [&](int k0) {
+    const int kend = K - k0 < KC ? K - k0 : KC;
+#pragma unroll 1
+    for (int i = 0; i < MM; ++i) {
+      const int64_t m = m0 + tm * MM + i < M ? m0 + tm * MM + i : 0;
+      const int rem = (int)(m % ((int64_t)Hc * Wc)), y = rem / Wc, x = rem - y * Wc;
+      const int hp = DATA ? (y * S + ph + g.pad - rf) / S : y * g.stride - g.pad, wp = DATA ? (x * S + pw + g.pad - sf) / S : x * g.stride - g.pad;
+#pragma unroll 1
+      for (int k = 0; k < kend; ++k) {
+        const int tap = (k0 + k) / Ca, r = tap / nsd, s = tap - r * nsd;
+        const int h = DATA ? hp - r : hp + r, c = DATA ? wp - s : wp + s;
+        if (h < 0 || c < 0 || h >= Ha || c >= Wa) continue;
+        for (int j = 0; j < MN; ++j) {
+          const double v = (double)As[k][tm * MM + i] * (double)Bs[k][tn * MN + j];
+          for (int u = 0; u < MM; ++u)            // (constant indices: the sums stay in registers)
+            if (u == i) acc[u][j] += v;
+        }
+      }
+    }
+  };
+  if (tid == 0) test_taps = 0;
   fetch(0);
+  __syncthreads();
   for (int k0 = 0; k0 < K; k0 += KC) {
     stash();
     __syncthreads();
     if (k0 + KC < K) fetch(k0 + KC);
+    if (test_taps) {
+      tested_chunk(k0);
+      __syncthreads();
+      continue;
+    }
 #pragma unroll 8
     for (int k = 0; k < KC; ++k) {
       double av[MM], bv[MN];
@@ -164,6 +199,7 @@ dat_status launch_direct(const float* a, const float* w, const float* res, float
 __global__ __launch_bounds__(kT) void direct_wgrad_kernel(const float* __restrict__ x, const float* __restrict__ dy, double* __restrict__ ws,
                                                           ConvGeom g, int64_t pps) {
   __shared__ __attribute__((aligned(16))) float As[KC][34], Bs[KC][34];        // dY[pixel][co], X[pixel][j]
+  __shared__ int test_taps;                                                     // a gradient that is not finite has been staged
   const int tid = threadIdx.x;
   const int J = g.k * g.k * g.Cin;
   const int c0 = blockIdx.x * 32, j0 = blockIdx.y * 32;
@@ -187,12 +223,41 @@ __global__ __launch_bounds__(kT) void direct_wgrad_kernel(const float* __restric
   };
   const int tn = tid % 16, tm = tid / 16;
   double acc[2][2] = {{0.0, 0.0}, {0.0, 0.0}};
+  // one chunk, leaving out the taps that lie outside the image
+  auto tested_chunk = [&](int64_t pb) {
+    const int kend = p1 - pb < KC ? (int)(p1 - pb) : KC;
+#pragma unroll 1
+    for (int q = 0; q < 2; ++q) {
+      const int jj = j0 + tn * 2 + q, jt = (jj < J ? jj : 0) / g.Cin, jr = jt / g.k, js = jt - jr * g.k;
+#pragma unroll 1
+      for (int k = 0; k < kend; ++k) {
+        const int rem = (int)((pb + k) % ((int64_t)g.Ho * g.Wo)), ho = rem / g.Wo, wo = rem - ho * g.Wo;
+        const int h = ho * g.stride + jr - g.pad, w = wo * g.stride + js - g.pad;
+        if (h < 0 || w < 0 || h >= g.H || w >= g.W) continue;
+        for (int i = 0; i < 2; ++i) {
+          const double v = (double)As[k][tm * 2 + i] * (double)Bs[k][tn * 2 + q];
+          for (int u = 0; u < 2; ++u)             // (constant indices: the sums stay in registers)
+            if (u == q) acc[i][u] += v;
+        }
+      }
+    }
+  };
+  if (tid == 0) test_taps = 0;
   fetch(p0);
+  __syncthreads();
   for (int64_t pb = p0; pb < p1; pb += KC) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) { As[row + 8 * i][col] = ra[i]; Bs[row + 8 * i][col] = rb[i]; }
+    for (int i = 0; i < 4; ++i) {
+      if (not_finite(ra[i])) test_taps = 1;
+      As[row + 8 * i][col] = ra[i]; Bs[row + 8 * i][col] = rb[i];
+    }
     __syncthreads();
     if (pb + KC < p1) fetch(pb + KC);
+    if (test_taps) {
+      tested_chunk(pb);
+      __syncthreads();
+      continue;
+    }
 #pragma unroll 8
     for (int k = 0; k < KC; ++k) {
       const float2 af = *reinterpret_cast<const float2*>(&As[k][tm * 2]), bf = *reinterpret_cast<const float2*>(&Bs[k][tn * 2]);
