@@ -334,7 +334,7 @@ typedef enum { DAT_OPT_FUSE_BN_INPUT_GRAD = 0, DAT_OPT_FUSE_BN_SUMS = 1, DAT_OPT
                DAT_OPT_ABSORB_SHORTCUT_BN = 5, DAT_OPT_FUSE_STEM_POOL = 6, DAT_OPT_GRADIENT_SCALES = 7,
                DAT_OPT_KEEP_BOTH_PASSES = 8 } dat_option;
 dat_status dat_model_set_option(dat_model* m, dat_option opt, int value);
-/* Process-wide kernel selection (ablations and tests; an atomic flag, read at every convolution launch of every
+/* Process-wide kernel selection (ablations and tests; atomic flags, read once per convolution of every
  * model and of the dat_conv_* entry points).  With an option off its layers run in 128-channel tiles of the
  * single-stage kernels; the convolution outputs are bit-identical, the grouping of the batch-norm partial sums differs.
  * DAT_KOPT_RING_KERNEL (default 1): long contractions that are one round of 256-channel tiles go through the
@@ -345,6 +345,15 @@ dat_status dat_model_set_option(dat_model* m, dat_option opt, int value);
  * through the multi-stage kernel, in tiles the narrower the fewer there are. */
 typedef enum { DAT_KOPT_RING_KERNEL = 0, DAT_KOPT_TILE_160 = 1, DAT_KOPT_NARROW_UNDERFILLED = 2 } dat_kernel_option;
 dat_status dat_set_kernel_option(dat_kernel_option opt, int value);
+
+/* What dat_conv_forward (pass 0) or dat_conv_backward_data (pass 1) would launch for a shape under the present switches;
+ * launches nothing and needs no GPU (256 compute units are taken where there is none).  `stats`: what a model asks of the
+ * epilogue, 0 nothing, 1 batch statistics (forward), 2 or 3 the sums of one or two batch normalisations' backward passes
+ * (backward-data).  info[10] = launches; of the last one: kernel (0 register-staged, 1 single-stage direct-to-LDS, 2
+ * multi-stage), channels and pixels per tile, LDS stages, channels per k-tile, 1 if a k-tile can straddle filter taps,
+ * parity classes in the launch (0: an ordinary one); then the slabs of partial sums the launches write and the slabs the
+ * reduction that follows reads. */
+dat_status dat_conv_plan(int pass, int stats, int B, int H, int W, int Cin, int Cout, int k, int stride, int pad, int32_t* info);
 
 /* ---- introspection for parity tests (not part of the paper's method) --------------------------------
  * The layer graph and the tensors a model keeps on the device, so that a test can compare every stored

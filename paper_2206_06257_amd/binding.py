@@ -22,7 +22,7 @@ EXPORTS = [
     "dat_quantized_bytes", "dat_conv_forward", "dat_conv_backward_data", "dat_conv_backward_weight",
     "dat_status_string", "dat_last_error", "dat_philox_uniform", "dat_profile_enable", "dat_profile_read", "dat_aggregate", "dat_lamb_update",
     "dat_attack_kl", "dat_step_reg", "dat_model_set_option", "dat_make_xadv",
-    "dat_conv_backward_weight_static", "dat_conv_backward_weight_static_limit", "dat_set_kernel_option", "dat_model_grad_scales", "dat_quantize_scaled",
+    "dat_conv_backward_weight_static", "dat_conv_backward_weight_static_limit", "dat_set_kernel_option", "dat_conv_plan", "dat_model_grad_scales", "dat_quantize_scaled",
     "dat_inspect_counts", "dat_inspect_op", "dat_inspect_tensor", "dat_inspect_read", "dat_inspect_bn",
 ]
 
@@ -103,6 +103,7 @@ KOPT_RING_KERNEL = 0
 KOPT_TILE_160 = 1
 KOPT_NARROW_UNDERFILLED = 2
 _lib.dat_set_kernel_option.argtypes = [_i, _i]
+_lib.dat_conv_plan.argtypes = [_i] * 10 + [_vp]
 _lib.dat_profile_read.argtypes = [_vp, _i, C.POINTER(C.c_double), C.POINTER(_i64), C.POINTER(C.c_double)]
 PROF_CLASSES = ("conv_fwd", "conv_bwd_data", "conv_wgrad", "bn", "pgd", "conv_bwd_data_bn")
 
@@ -395,6 +396,14 @@ def philox_uniform(start, n, seed, stream_id, device="cuda"):
 
 def _conv_shapes(B, H, W, Cin, Cout, k, stride, pad):
     return (H + 2 * pad - k) // stride + 1, (W + 2 * pad - k) // stride + 1
+
+
+def conv_plan(shape, backward=False, stats=0):
+    """What conv_forward / conv_backward_data would launch for (B, H, W, Cin, Cout, k, stride, pad): see dat_conv_plan."""
+    info = np.zeros(10, np.int32)
+    _check(_lib.dat_conv_plan(int(bool(backward)), stats, *[int(v) for v in shape], info.ctypes.data), "dat_conv_plan")
+    names = ("launches", "kernel", "tile_c", "tile_p", "stages", "k_tile", "straddle", "classes", "slabs_written", "slabs_read")
+    return dict(zip(names, (int(v) for v in info)))
 
 
 def conv_forward(x, w, stride, pad, stream=None):

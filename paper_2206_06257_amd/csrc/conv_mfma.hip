@@ -134,6 +134,21 @@ __device__ __forceinline__ int enter_class(IgemmArgs& a, const IgemmClasses& cl,
   return bid - begin;
 }
 
+// dat_conv_plan: while set, the launches of this thread are noted here instead of being made.
+struct LaunchRecord { int launches, kernel, tile_c, tile_p, stages, k_tile, straddle, classes; int64_t slabs; };
+thread_local LaunchRecord* t_record = nullptr;
+enum { kRegisterStaged = 0, kSingleStage = 1, kMultiStage = 2 };
+
+bool recorded(const IgemmArgs& a, const IgemmClasses& cl, int kernel, int tile_c, int tile_p, int stages, int k_tile, int straddle) {
+  if (!t_record) return false;
+  LaunchRecord& r = *t_record;
+  ++r.launches;
+  r.kernel = kernel; r.tile_c = tile_c; r.tile_p = tile_p; r.stages = stages; r.k_tile = k_tile; r.straddle = straddle; r.classes = cl.n;
+  if (!cl.n) r.slabs += a.npt;
+  for (int i = 0; i < cl.n; ++i) r.slabs += cl.c[i].npt;
+  return true;
+}
+
 __device__ __forceinline__ int64_t out_row(const IgemmArgs& a, int m) {
   if (a.ostep == 1 && a.outH == a.Hout && a.outW == a.Wout) return m;
   const int HW = a.Hout * a.Wout;
@@ -742,6 +757,7 @@ dat_status launch_igemm_dma(IgemmArgs a, hipStream_t st, IgemmClasses cl = Igemm
   const unsigned blocks = plan_blocks<TP>(a, cl);
   if (blocks == 0) return DAT_OK;
   a.xcd_contiguous = a.KH * a.KW > 1;   // filter windows: neighbouring tiles re-read each other's rows
+  if (recorded(a, cl, kSingleStage, TC, TP, 1, BKT, 0)) return DAT_OK;
   hipLaunchKernelGGL((igemm_dma_kernel<TC, TP, WGC, OCC, BKT>), dim3(blocks), dim3(kThreads), 0, st, a, cl);
   DAT_LAUNCH_CHECK();
   return DAT_OK;
@@ -949,6 +965,7 @@ dat_status launch_igemm_ring(IgemmArgs a, hipStream_t st, IgemmClasses cl = Igem
   a.nct = (a.Cout + TC - 1) / TC;
   const unsigned blocks = plan_blocks<TP>(a, cl);
   if (blocks == 0) return DAT_OK;
+  if (recorded(a, cl, kMultiStage, TC, TP, S, 64, ANYC)) return DAT_OK;
   hipLaunchKernelGGL((igemm_ring_kernel<TC, TP, WGC, S, NT, G, ANYC>), dim3(blocks), dim3(NT), 0, st, a, cl);
   DAT_LAUNCH_CHECK();
   return DAT_OK;
@@ -971,6 +988,7 @@ dat_status launch_igemm_xf(IgemmArgs a, hipStream_t st) {
   a.npt = (a.M + TP - 1) / TP;
   if (a.npt == 0) return DAT_OK;
   a.xcd_contiguous = 0;
+  if (recorded(a, IgemmClasses{}, kRegisterStaged, TC, TP, 1, BKT, 0)) return DAT_OK;
   const int npt8 = (a.npt + 7) / 8 * 8;
   hipLaunchKernelGGL((igemm_kernel<TC, TP, WGC, PF, true, BKT, OCC, true>), dim3((unsigned)(npt8 * a.nct)), dim3(kThreads), tab_bytes, st, a);
   DAT_LAUNCH_CHECK();
@@ -985,6 +1003,7 @@ dat_status launch_igemm(IgemmArgs a, hipStream_t st) {
   a.npt = (a.M + TP - 1) / TP;
   if (a.npt == 0) return DAT_OK;
   a.xcd_contiguous = a.KH * a.KW > 1;   // filter windows: neighbouring tiles re-read each other's rows
+  if (recorded(a, IgemmClasses{}, kRegisterStaged, TC, TP, 1, BKT, a.Cin % BKT != 0)) return DAT_OK;
   const int npt8 = (a.npt + 7) / 8 * 8;
   if (a.Cin % BKT == 0 && a.Ktot > 0)
     hipLaunchKernelGGL((igemm_kernel<TC, TP, WGC, PF, true, BKT, OCC>), dim3((unsigned)(npt8 * a.nct)), dim3(kThreads), 0, st, a);
@@ -1029,6 +1048,13 @@ std::atomic<bool> g_ring_enabled{true};
 std::atomic<bool> g_tile160{true};
 std::atomic<bool> g_narrow_underfilled{true};
 
+// The switches of dat_set_kernel_option, read once per convolution: the slab count a reduction is given and the tiles that
+// write the slabs follow from the same values, whatever another thread sets meanwhile.
+struct Switches { bool ring, tile160, narrow; };
+Switches read_switches() {
+  return {g_ring_enabled.load(std::memory_order_relaxed), g_tile160.load(std::memory_order_relaxed), g_narrow_underfilled.load(std::memory_order_relaxed)};
+}
+
 // Which ring configuration, if any, runs this launch.  The lines are drawn by tiles per CU (256 CUs), measured on the
 // 3x3 and 1x1 layers of every network at batches of 13 to 512, us:
 //  * kR160x256 / kR160x128: widths that are a multiple of 160 (the wide ResNets).  Every wave takes all 160 channels of 32
@@ -1044,11 +1070,11 @@ std::atomic<bool> g_narrow_underfilled{true};
 //    images 48.8 -> 19.6; 64x128 25.6).
 enum RingPick { kRNone, kR32, kR64, kR128, kR256x128, kR256x256, kR160x128, kR160x256, kR160x128Any, kR160x256Any };
 
-RingPick pick_ring(const IgemmArgs& a) {
+RingPick pick_ring(const IgemmArgs& a, const Switches& sw) {
   if (a.xf_tab || a.xstride || a.Cin % 8 != 0 || a.Ktot < 256 || a.KH * a.KW * a.Cin != a.Ktot) return kRNone;
   const int64_t cus = compute_units(), p128 = ((int64_t)a.M + 127) / 128, p256 = ((int64_t)a.M + 255) / 256;
   const bool one_grid = a.ostep == 1 && a.stat_slab0 == 0;       // 256-pixel tiles: the whole tensor is this launch
-  if (a.Cout % 160 == 0 && (a.Cin % 64 == 0 || a.Ktot >= 512) && g_tile160.load(std::memory_order_relaxed)) {
+  if (a.Cout % 160 == 0 && (a.Cin % 64 == 0 || a.Ktot >= 512) && sw.tile160) {
     const int64_t per_cu = (p128 * (a.Cout / 160) + cus - 1) / cus;
     const bool any = a.Cin % 64 != 0;
     // 640 channels over few pixels: 128 divides them too, and the narrower tiles below give more CUs work
@@ -1058,12 +1084,12 @@ RingPick pick_ring(const IgemmArgs& a) {
     }
   }
   if (a.Cin % 64 != 0) return kRNone;
-  if (one_grid && a.Ktot >= 1024 && a.Cout % 256 == 0 && g_ring_enabled.load(std::memory_order_relaxed)) {
+  if (one_grid && a.Ktot >= 1024 && a.Cout % 256 == 0 && sw.ring) {
     const int64_t nct = a.Cout / 256, t256 = p256 * nct, t128 = p128 * nct;
     if (t256 <= cus && 5 * t256 >= 3 * cus) return kR256x256;
     if (t128 <= cus && 2 * t128 >= cus) return kR256x128;
   }
-  if (!g_narrow_underfilled.load(std::memory_order_relaxed)) return kRNone;
+  if (!sw.narrow) return kRNone;
   // A backward-data pass that igemm_kernel may also run with its operand transform (conv_mfma_bn_operand_ok) leaves its
   // batch-norm sums in the same order either way: 64-channel tiles of 256 threads, or the 128-channel single-stage kernel.
   if (a.stat_mode >= 2 && a.KH * a.KW == 1 && a.ostep == 1 && a.Cout > 32 && a.Cout <= 128 && a.Cin >= 2 * a.Cout)
@@ -1074,21 +1100,20 @@ RingPick pick_ring(const IgemmArgs& a) {
   return kRNone;
 }
 
-// pixel rows per tile (= per slab of epilogue statistics) of the configuration run_igemm selects
-int pixel_tile(const IgemmArgs& a) {
-  const RingPick r = pick_ring(a);
+// pixel rows per tile (= per slab of epilogue statistics) of the configuration run_igemm launches
+int pixel_tile(RingPick r) {
   return r == kR256x256 || r == kR160x256 || r == kR160x256Any ? 256 : 128;
 }
 
-dat_status run_igemm(const IgemmArgs& a, hipStream_t st) {
-  g_launches.fetch_add(1, std::memory_order_relaxed);
+dat_status run_igemm(const IgemmArgs& a, const Switches& sw, RingPick ring, hipStream_t st) {
+  if (!t_record) g_launches.fetch_add(1, std::memory_order_relaxed);
   if (a.Cin % 8 != 0 || a.Cout % 8 != 0) return DAT_ERR_UNSUPPORTED;
   if (a.stat_mode == 3 && (a.Cout <= 64 || a.xf_tab)) return DAT_ERR_UNSUPPORTED;   // three sums: 128-channel tiles only
   if (a.xstride) {   // overlapping input pixels: the direct-to-LDS kernel with one tap per 64-wide k-tile
     if (a.Cout > 64 || a.xf_tab) return DAT_ERR_UNSUPPORTED;
     return a.Cout <= 32 ? launch_igemm_dma<32, 128, 1, 6>(a, st) : launch_igemm_dma<64, 128, 2, 5>(a, st);
   }
-  switch (pick_ring(a)) {
+  switch (ring) {
     case kR32: return launch_igemm_ring<32, 128, 1, 4, 256, 4>(a, st);
     case kR64: return launch_igemm_ring<64, 128, 2, 3, 256, 4>(a, st);
     case kR128: return launch_igemm_ring<128, 128, 2, 4, 512, 4>(a, st);
@@ -1108,7 +1133,7 @@ dat_status run_igemm(const IgemmArgs& a, hipStream_t st) {
     return launch_igemm_xf<128, 128, 2, 2, 32, 2>(a, st);
   }
   // short contractions into a multiple of 160 channels that 128 does not divide: 160-channel tiles
-  if (a.Cout % 160 == 0 && a.Cout % 128 != 0 && g_tile160.load(std::memory_order_relaxed)) return launch_igemm<160, 128, 1, 1, 32, 3>(a, st);
+  if (a.Cout % 160 == 0 && a.Cout % 128 != 0 && sw.tile160) return launch_igemm<160, 128, 1, 1, 32, 3>(a, st);
   // narrow channel tiles: the direct-to-LDS kernel wherever its k-tile divides the contraction channels,
   // except 1x1 layers with a long contraction into <= 64 channels (HBM-bound reads: deep register
   // prefetch with two workgroups per CU streams them at the copy rate)
@@ -1126,25 +1151,24 @@ dat_status run_igemm(const IgemmArgs& a, hipStream_t st) {
 
 // The classes of one backward-data pass as one launch, if a kernel takes them that way (*done); `a` carries the values of
 // the class with most taps.  128-pixel tiles; the rules are those of pick_ring and run_igemm for the sum of the tiles.
-dat_status run_igemm_classes(const IgemmArgs& a, const IgemmClasses& cl, hipStream_t st, bool* done) {
+dat_status run_igemm_classes(const IgemmArgs& a, const Switches& sw, const IgemmClasses& cl, hipStream_t st, bool* done) {
   *done = false;
-  const bool tile160 = a.Cout % 160 == 0 && g_tile160.load(std::memory_order_relaxed), any = a.Cin % 64 != 0;
+  const bool tile160 = a.Cout % 160 == 0 && sw.tile160, any = a.Cin % 64 != 0;
   if (any && !(tile160 && a.Ktot >= 512)) return DAT_OK;
   if (a.Ktot < 64 || a.Cin % 8 != 0 || a.Cout % 8 != 0 || a.xf_tab || a.xstride || (a.stat_mode == 3 && a.Cout <= 64)) return DAT_OK;
   *done = true;
-  g_launches.fetch_add(1, std::memory_order_relaxed);
+  if (!t_record) g_launches.fetch_add(1, std::memory_order_relaxed);
   int64_t tiles = 0;
   for (int i = 0; i < cl.n; ++i) tiles += (cl.c[i].M + 127) / 128;
   const int64_t cus = compute_units(), t = tiles * ((a.Cout + 127) / 128);
   if (any) return launch_igemm_ring<160, 128, 1, 2, 256, 1, true>(a, st, cl);
   if (tile160 && (a.Cout % 128 != 0 || 2 * tiles * (a.Cout / 160) > cus)) return launch_igemm_ring<160, 128, 1, 2, 256, 1>(a, st, cl);
-  const bool narrow = g_narrow_underfilled.load(std::memory_order_relaxed);
-  if (narrow && a.Cout > 64 && t <= cus) {
+  if (sw.narrow && a.Cout > 64 && t <= cus) {
     if (2 * t > cus) return launch_igemm_ring<128, 128, 2, 4, 512, 4>(a, st, cl);
     if (4 * t > cus) return launch_igemm_ring<64, 128, 2, 3, 256, 4>(a, st, cl);
     return launch_igemm_ring<32, 128, 1, 4, 256, 4>(a, st, cl);
   }
-  if (narrow && a.Cout <= 64 && 2 * tiles <= cus) return launch_igemm_ring<32, 128, 1, 4, 256, 4>(a, st, cl);
+  if (sw.narrow && a.Cout <= 64 && 2 * tiles <= cus) return launch_igemm_ring<32, 128, 1, 4, 256, 4>(a, st, cl);
   if (a.Cout <= 32) return launch_igemm_dma<32, 128, 1, 6>(a, st, cl);
   if (a.Cout <= 64) return launch_igemm_dma<64, 128, 2, 5>(a, st, cl);
   return launch_igemm_dma<128, 128, 2, 4>(a, st, cl);
@@ -1602,8 +1626,10 @@ dat_status conv_mfma_forward(const bf16_t* x, const bf16_t* w, const bf16_t* res
   a.outH = g.Ho; a.outW = g.Wo; a.ostep = 1; a.oh0 = a.ow0 = 0;
   a.M = g.B * g.Ho * g.Wo; a.Ktot = g.k * g.k * g.Cin; a.nct = a.npt = 0;
   set_stats(a, stats, 0);
-  if (stats) stats->nslabs = (a.M + pixel_tile(a) - 1) / pixel_tile(a);
-  return run_igemm(a, st);
+  const Switches sw = read_switches();
+  const RingPick ring = pick_ring(a, sw);
+  if (stats) stats->nslabs = (a.M + pixel_tile(ring) - 1) / pixel_tile(ring);
+  return run_igemm(a, sw, ring, st);
 }
 
 bool conv_mfma_sparse_writer_ok(const ConvGeom& g) { return g.k == 1 && g.stride == 2 && g.pad == 0; }
@@ -1636,13 +1662,16 @@ dat_status conv_mfma_backward_data(const bf16_t* dy, const bf16_t* wT, bf16_t* d
     a.ostep = 1; a.oh0 = a.ow0 = 0;
     a.M = g.B * g.H * g.W; a.Ktot = g.k * g.k * g.Cout;
     set_stats(a, stats, 0);
-    if (stats) stats->nslabs = (a.M + pixel_tile(a) - 1) / pixel_tile(a);
-    return run_igemm(a, st);
+    const Switches sw = read_switches();
+    const RingPick ring = pick_ring(a, sw);
+    if (stats) stats->nslabs = (a.M + pixel_tile(ring) - 1) / pixel_tile(ring);
+    return run_igemm(a, sw, ring, st);
   }
   if (g.stride != 2) return DAT_ERR_UNSUPPORTED;
   a.ostep = 2;
   set_stats(a, stats, 0);
   const bf16_t* const stored = a.res;
+  const Switches sw = read_switches();
   IgemmClass cls[4];
   int n = 0, slab0 = 0;
   int64_t base = 0;
@@ -1681,12 +1710,12 @@ dat_status conv_mfma_backward_data(const bf16_t* dy, const bf16_t* wT, bf16_t* d
     take(cl.c[0]);
     a.res = stored;
     bool done;
-    const dat_status s = run_igemm_classes(a, cl, st, &done);
+    const dat_status s = run_igemm_classes(a, sw, cl, st, &done);
     if (done) { if (stats) stats->nslabs = slab0; return s; }
   }
   for (int i = 0; i < n; ++i) {
     take(cls[i]);
-    const dat_status s = run_igemm(a, st);
+    const dat_status s = run_igemm(a, sw, pick_ring(a, sw), st);
     if (s != DAT_OK) return s;
   }
   if (stats) stats->nslabs = slab0;
@@ -1723,7 +1752,7 @@ dat_status conv_mfma_stem_forward(const bf16_t* x2, const bf16_t* vf, bf16_t* y,
   a.M = g.B * g.Ho * g.Wo; a.Ktot = 16 * kStemV; a.nct = a.npt = 0;
   set_stats(a, stats, 0);
   if (stats) stats->nslabs = (a.M + kPixelTile - 1) / kPixelTile;
-  return run_igemm(a, st);
+  return run_igemm(a, read_switches(), kRNone, st);      // (run_igemm takes a row read as one tap first)
 }
 
 dat_status conv_mfma_stem_backward_data(const bf16_t* dy, const bf16_t* vb, bf16_t* dx2, const ConvGeom& g, bool accumulate, hipStream_t st) {
@@ -1736,7 +1765,8 @@ dat_status conv_mfma_stem_backward_data(const bf16_t* dy, const bf16_t* vb, bf16
   a.outH = a.Hout; a.outW = a.Wout; a.ostep = 1; a.oh0 = a.ow0 = 0;
   a.M = g.B * a.Hout * a.Wout; a.Ktot = 16 * g.Cout; a.nct = a.npt = 0;
   set_stats(a, nullptr, 0);
-  return run_igemm(a, st);
+  const Switches sw = read_switches();
+  return run_igemm(a, sw, pick_ring(a, sw), st);
 }
 
 dat_status conv_mfma_backward_weight(const bf16_t* x, const bf16_t* dy, float* dw, int cin_real, const ConvGeom& g, float scale,
@@ -1808,6 +1838,22 @@ static bool geom_from(int B, int H, int W, int Cin, int Cout, int k, int stride,
   if (g->Ho < 1 || g->Wo < 1) return false;
   if ((int64_t)B * H * W * Cin >= (1ll << 31) || (int64_t)B * g->Ho * g->Wo * Cout >= (1ll << 31)) return false;
   return true;
+}
+
+extern "C" dat_status dat_conv_plan(int pass, int stats, int B, int H, int W, int Cin, int Cout, int k, int stride, int pad, int32_t* info) {
+  ConvGeom g;
+  if (!info || pass < 0 || pass > 1 || stats < 0 || stats > 3 || (pass == 0 && stats > 1) || !geom_from(B, H, W, Cin, Cout, k, stride, pad, &g)) return DAT_ERR_ARG;
+  ConvStats cs{};
+  cs.mode = stats;
+  LaunchRecord r{};
+  t_record = &r;
+  const dat_status s = pass == 0 ? conv_mfma_forward(nullptr, nullptr, nullptr, nullptr, g, &cs, nullptr)
+                                 : conv_mfma_backward_data(nullptr, nullptr, nullptr, g, false, &cs, nullptr);
+  t_record = nullptr;
+  if (s != DAT_OK) return s;
+  const int32_t v[10] = {r.launches, r.kernel, r.tile_c, r.tile_p, r.stages, r.k_tile, r.straddle, r.classes, (int32_t)r.slabs, cs.nslabs};
+  for (int i = 0; i < 10; ++i) info[i] = v[i];
+  return DAT_OK;
 }
 
 extern "C" dat_status dat_conv_forward(const uint16_t* x, const uint16_t* w, uint16_t* y, int B, int H, int W, int Cin,

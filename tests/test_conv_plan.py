@@ -1,0 +1,54 @@
+"""The rules that pick a convolution's kernel and tile, through dat_conv_plan (host code only: runs without a GPU)."""
+import sys
+import threading
+
+import numpy as np
+import pytest
+
+import paper_2206_06257_amd as dat
+from paper_2206_06257_amd import binding
+
+OPTIONS = (dat.KOPT_RING_KERNEL, dat.KOPT_TILE_160, dat.KOPT_NARROW_UNDERFILLED)
+
+
+@pytest.fixture(autouse=True)
+def _default_switches():
+    yield
+    for o in OPTIONS:
+        dat.set_kernel_option(o, 1)
+
+
+def test_slabs_written_are_the_slabs_read_while_a_switch_changes():
+    """The switches are read once per convolution: a change from another thread between the slab count and the launch would
+    leave the batch-norm sums short of slabs, or with stale ones."""
+    shapes = [(256, 14, 14, 256, 256, 3, 1, 1), (512, 16, 16, 320, 320, 3, 1, 1)]   # 256-pixel tiles with a switch on, 128 with it off
+    for s, o in zip(shapes, OPTIONS):
+        assert dat.conv_plan(s, stats=1)["tile_p"] == 256
+        dat.set_kernel_option(o, 0)
+        assert dat.conv_plan(s, stats=1)["tile_p"] == 128
+        dat.set_kernel_option(o, 1)
+    stop, interval, info = threading.Event(), sys.getswitchinterval(), np.zeros(10, np.int32)
+    set_option, plan, out = binding._lib.dat_set_kernel_option, binding._lib.dat_conv_plan, info.ctypes.data
+
+    def toggle():
+        while not stop.is_set():
+            for v in (0, 1):
+                set_option(OPTIONS[0], v)
+                set_option(OPTIONS[1], v)
+
+    threads = [threading.Thread(target=toggle) for _ in range(3)]
+    sys.setswitchinterval(1e-7)
+    for t in threads:
+        t.start()
+    try:
+        tiles, bad = set(), 0
+        for i in range(80000):
+            assert plan(i >> 1 & 1, 1 + (i >> 1 & 1), *shapes[i & 1], out) == 0
+            tiles.add(int(info[3]))
+            bad += int(info[8]) != int(info[9])
+    finally:
+        stop.set()
+        for t in threads:
+            t.join()
+        sys.setswitchinterval(interval)
+    assert tiles == {128, 256} and bad == 0
