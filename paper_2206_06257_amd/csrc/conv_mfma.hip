@@ -112,26 +112,25 @@ struct IgemmArgs {
 // backward-data pass go this way, the classes with most taps first (their workgroups run longest).  Each class has
 // blocks [begin, next begin), a multiple of 8, so the tile numbering inside a class is that of a launch of its own.
 struct IgemmClass { const bf16_t* wt; int Hout, Wout, KH, KW, pad_h, pad_w, oh0, ow0, M, Ktot, stat_slab0, with_res, npt, begin; };
-struct IgemmClasses { int n; IgemmClass c[4]; };      // n = 0: an ordinary launch
+struct IgemmClasses { int n; IgemmClass c[4]; };
+// An ordinary launch: a kernel of its own, without the table.  With the table as an argument of every launch and all four
+// entries read (n = 0: none), the 64- and 32-channel single-stage kernels spilled 9 and 8 vector registers instead of 2 and 4
+// and the 256 x 256 multi-stage kernel 16 scalar ones.  (Over 500 layer shapes: ordinary launches 0 to 1.5 % faster without
+// it, launches in classes 1 to 2 % since they read their own entry only.)
+struct NoClasses { static constexpr int n = 0; };
 
-// Block number within its class, whose values replace those of `a`.
+__device__ __forceinline__ int enter_class(IgemmArgs&, const NoClasses&, int bid) { return bid; }
+// Block number within its class, whose values replace those of `a` (read from the argument block at an index that is the
+// same for all lanes: scalar loads of one class only).
 __device__ __forceinline__ int enter_class(IgemmArgs& a, const IgemmClasses& cl, int bid) {
-  int begin = 0;
+  int k = 0;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {          // (constant indices: the arguments stay in scalar registers)
-    const IgemmClass& c = cl.c[i];
-    if (i < cl.n && bid >= c.begin) {
-      a.wt = c.wt; a.Hout = c.Hout; a.Wout = c.Wout; a.KH = c.KH; a.KW = c.KW; a.pad_h = c.pad_h; a.pad_w = c.pad_w;
-      a.oh0 = c.oh0; a.ow0 = c.ow0; a.M = c.M; a.Ktot = c.Ktot; a.stat_slab0 = c.stat_slab0; a.npt = c.npt;
-      begin = c.begin;
-    }
-  }
-  bool with_res = true;
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-    if (i < cl.n && bid >= cl.c[i].begin) with_res = cl.c[i].with_res != 0;
-  if (!with_res) a.res = nullptr;
-  return bid - begin;
+  for (int i = 1; i < 4; ++i) k += i < cl.n && bid >= cl.c[i].begin;
+  const IgemmClass& c = cl.c[k];
+  a.wt = c.wt; a.Hout = c.Hout; a.Wout = c.Wout; a.KH = c.KH; a.KW = c.KW; a.pad_h = c.pad_h; a.pad_w = c.pad_w;
+  a.oh0 = c.oh0; a.ow0 = c.ow0; a.M = c.M; a.Ktot = c.Ktot; a.stat_slab0 = c.stat_slab0; a.npt = c.npt;
+  if (!c.with_res) a.res = nullptr;
+  return bid - c.begin;
 }
 
 // dat_conv_plan: while set, the launches of this thread are noted here instead of being made.
@@ -139,13 +138,16 @@ struct LaunchRecord { int launches, kernel, tile_c, tile_p, stages, k_tile, stra
 thread_local LaunchRecord* t_record = nullptr;
 enum { kRegisterStaged = 0, kSingleStage = 1, kMultiStage = 2 };
 
-bool recorded(const IgemmArgs& a, const IgemmClasses& cl, int kernel, int tile_c, int tile_p, int stages, int k_tile, int straddle) {
+int64_t slabs_of(const IgemmArgs& a, const NoClasses&) { return a.npt; }
+int64_t slabs_of(const IgemmArgs&, const IgemmClasses& cl) { int64_t s = 0; for (int i = 0; i < cl.n; ++i) s += cl.c[i].npt; return s; }
+
+template <class CL>
+bool recorded(const IgemmArgs& a, const CL& cl, int kernel, int tile_c, int tile_p, int stages, int k_tile, int straddle) {
   if (!t_record) return false;
   LaunchRecord& r = *t_record;
   ++r.launches;
   r.kernel = kernel; r.tile_c = tile_c; r.tile_p = tile_p; r.stages = stages; r.k_tile = k_tile; r.straddle = straddle; r.classes = cl.n;
-  if (!cl.n) r.slabs += a.npt;
-  for (int i = 0; i < cl.n; ++i) r.slabs += cl.c[i].npt;
+  r.slabs += slabs_of(a, cl);
   return true;
 }
 
@@ -615,8 +617,8 @@ __device__ __forceinline__ void load_to_lds(BufRsrc r, unsigned char* dst, uint3
   __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void_ptr)dst, 16, (int)lane_off, (int)uniform_off, 0, 0);
 }
 
-template <int TC, int TP, int WGC, int OCC, int BKT>
-__global__ __launch_bounds__(kThreads, OCC) void igemm_dma_kernel(IgemmArgs a, IgemmClasses cl) {
+template <int TC, int TP, int WGC, int OCC, int BKT, class CL>
+__global__ __launch_bounds__(kThreads, OCC) void igemm_dma_kernel(IgemmArgs a, CL cl) {
   constexpr int KS = BKT / 16, NS = BKT / 8;              // MFMA k-steps per tile; 16-byte slots per tile row
   constexpr int WGP = 4 / WGC;
   constexpr int WC = TC / WGC, WP = TP / WGP;
@@ -632,8 +634,7 @@ __global__ __launch_bounds__(kThreads, OCC) void igemm_dma_kernel(IgemmArgs a, I
   static_assert(TP % RPG == 0 && (BKT == 32 || BKT == 64), "tile rows must be whole load sweeps");
   __shared__ __attribute__((aligned(1024))) unsigned char lds[LDS_BYTES];
 
-  int bid = blockIdx.x;
-  if (cl.n) bid = enter_class(a, cl, bid);
+  const int bid = enter_class(a, cl, blockIdx.x);
   const int q = bid >> 3;
   const int ct = q % a.nct;
   const int pt = a.xcd_contiguous ? (bid & 7) * ((a.npt + 7) >> 3) + (q / a.nct) : (q / a.nct) * 8 + (bid & 7);
@@ -737,8 +738,12 @@ __global__ __launch_bounds__(kThreads, OCC) void igemm_dma_kernel(IgemmArgs a, I
 
 // Blocks of a launch in tiles of TP pixels; for a launch in classes also their block ranges.
 template <int TP>
+unsigned plan_blocks(IgemmArgs& a, NoClasses&) {
+  a.npt = (a.M + TP - 1) / TP;
+  return (unsigned)((a.npt + 7) / 8 * 8 * a.nct);
+}
+template <int TP>
 unsigned plan_blocks(IgemmArgs& a, IgemmClasses& cl) {
-  if (!cl.n) { a.npt = (a.M + TP - 1) / TP; return (unsigned)((a.npt + 7) / 8 * 8 * a.nct); }
   int blocks = 0;
   for (int i = 0; i < cl.n; ++i) {
     cl.c[i].npt = (cl.c[i].M + TP - 1) / TP;
@@ -748,8 +753,8 @@ unsigned plan_blocks(IgemmArgs& a, IgemmClasses& cl) {
   return (unsigned)blocks;
 }
 
-template <int TC, int TP, int WGC, int OCC, int BKT = 64>
-dat_status launch_igemm_dma(IgemmArgs a, hipStream_t st, IgemmClasses cl = IgemmClasses{}) {
+template <int TC, int TP, int WGC, int OCC, int BKT = 64, class CL = NoClasses>
+dat_status launch_igemm_dma(IgemmArgs a, hipStream_t st, CL cl = CL{}) {
   if ((int64_t)a.B * a.Hin * a.Win * a.Cin >= (1ll << 31) || (int64_t)a.Cout * a.Ktot >= (1ll << 31)) return DAT_ERR_UNSUPPORTED;
   if (a.Cin % BKT != 0 || a.Ktot < BKT || a.Ktot % BKT != 0) return DAT_ERR_UNSUPPORTED;
   if (a.xstride && (a.Cin != BKT || a.xstride % 8 != 0 || a.Cin % a.xstride != 0)) return DAT_ERR_UNSUPPORTED;   // one tap per k-tile
@@ -758,7 +763,7 @@ dat_status launch_igemm_dma(IgemmArgs a, hipStream_t st, IgemmClasses cl = Igemm
   if (blocks == 0) return DAT_OK;
   a.xcd_contiguous = a.KH * a.KW > 1;   // filter windows: neighbouring tiles re-read each other's rows
   if (recorded(a, cl, kSingleStage, TC, TP, 1, BKT, 0)) return DAT_OK;
-  hipLaunchKernelGGL((igemm_dma_kernel<TC, TP, WGC, OCC, BKT>), dim3(blocks), dim3(kThreads), 0, st, a, cl);
+  hipLaunchKernelGGL((igemm_dma_kernel<TC, TP, WGC, OCC, BKT, CL>), dim3(blocks), dim3(kThreads), 0, st, a, cl);
   DAT_LAUNCH_CHECK();
   return DAT_OK;
 }
@@ -779,8 +784,8 @@ dat_status launch_igemm_dma(IgemmArgs a, hipStream_t st, IgemmClasses cl = Igemm
 // ANYC: the contraction channels are no multiple of the k-tile (160 channels, 64-wide tiles), so a tile straddles
 // filter taps: every lane follows the tap and channel of its own 16-byte vector (a vector never straddles: Cin % 8
 // == 0), and the last tile is padded with zeros.
-template <int TC, int TP, int WGC, int S, int NT, int G, bool ANYC = false>
-__global__ __launch_bounds__(NT) void igemm_ring_kernel(IgemmArgs a, IgemmClasses cl) {
+template <int TC, int TP, int WGC, int S, int NT, int G, bool ANYC, class CL>
+__global__ __launch_bounds__(NT) void igemm_ring_kernel(IgemmArgs a, CL cl) {
   constexpr int BKT = 64, KS = BKT / 16, NG = KS / G;       // MFMA k-steps per tile, in NG groups of G
   constexpr int WGP = NT / 64 / WGC;
   constexpr int WC = TC / WGC, WP = TP / WGP;
@@ -800,8 +805,7 @@ __global__ __launch_bounds__(NT) void igemm_ring_kernel(IgemmArgs a, IgemmClasse
   static_assert(LDS_BYTES <= 163840, "LDS of a CU");
   __shared__ __attribute__((aligned(1024))) unsigned char lds[LDS_BYTES];
 
-  int bid = blockIdx.x;
-  if (cl.n) bid = enter_class(a, cl, bid);
+  const int bid = enter_class(a, cl, blockIdx.x);
   const int q = bid >> 3;
   const int ct = q % a.nct, pt = (q / a.nct) * 8 + (bid & 7);
   if (pt >= a.npt) return;
@@ -957,8 +961,8 @@ __global__ __launch_bounds__(NT) void igemm_ring_kernel(IgemmArgs a, IgemmClasse
   igemm_epilogue<TC, TP, WGC, NT>(a, acc, lds, c0, m0, pt);
 }
 
-template <int TC, int TP, int WGC, int S, int NT, int G, bool ANYC = false>
-dat_status launch_igemm_ring(IgemmArgs a, hipStream_t st, IgemmClasses cl = IgemmClasses{}) {
+template <int TC, int TP, int WGC, int S, int NT, int G, bool ANYC = false, class CL = NoClasses>
+dat_status launch_igemm_ring(IgemmArgs a, hipStream_t st, CL cl = CL{}) {
   if ((int64_t)a.B * a.Hin * a.Win * a.Cin >= (1ll << 31) || (int64_t)a.Cout * a.Ktot >= (1ll << 31)) return DAT_ERR_UNSUPPORTED;
   if (a.Ktot < 64 || a.xf_tab || a.xstride) return DAT_ERR_UNSUPPORTED;
   if (ANYC ? (a.Cin % 8 != 0 || a.Ktot != a.KH * a.KW * a.Cin) : a.Cin % 64 != 0) return DAT_ERR_UNSUPPORTED;
@@ -966,7 +970,7 @@ dat_status launch_igemm_ring(IgemmArgs a, hipStream_t st, IgemmClasses cl = Igem
   const unsigned blocks = plan_blocks<TP>(a, cl);
   if (blocks == 0) return DAT_OK;
   if (recorded(a, cl, kMultiStage, TC, TP, S, 64, ANYC)) return DAT_OK;
-  hipLaunchKernelGGL((igemm_ring_kernel<TC, TP, WGC, S, NT, G, ANYC>), dim3(blocks), dim3(NT), 0, st, a, cl);
+  hipLaunchKernelGGL((igemm_ring_kernel<TC, TP, WGC, S, NT, G, ANYC, CL>), dim3(blocks), dim3(NT), 0, st, a, cl);
   DAT_LAUNCH_CHECK();
   return DAT_OK;
 }
@@ -988,7 +992,7 @@ dat_status launch_igemm_xf(IgemmArgs a, hipStream_t st) {
   a.npt = (a.M + TP - 1) / TP;
   if (a.npt == 0) return DAT_OK;
   a.xcd_contiguous = 0;
-  if (recorded(a, IgemmClasses{}, kRegisterStaged, TC, TP, 1, BKT, 0)) return DAT_OK;
+  if (recorded(a, NoClasses{}, kRegisterStaged, TC, TP, 1, BKT, 0)) return DAT_OK;
   const int npt8 = (a.npt + 7) / 8 * 8;
   hipLaunchKernelGGL((igemm_kernel<TC, TP, WGC, PF, true, BKT, OCC, true>), dim3((unsigned)(npt8 * a.nct)), dim3(kThreads), tab_bytes, st, a);
   DAT_LAUNCH_CHECK();
@@ -1003,7 +1007,7 @@ dat_status launch_igemm(IgemmArgs a, hipStream_t st) {
   a.npt = (a.M + TP - 1) / TP;
   if (a.npt == 0) return DAT_OK;
   a.xcd_contiguous = a.KH * a.KW > 1;   // filter windows: neighbouring tiles re-read each other's rows
-  if (recorded(a, IgemmClasses{}, kRegisterStaged, TC, TP, 1, BKT, a.Cin % BKT != 0)) return DAT_OK;
+  if (recorded(a, NoClasses{}, kRegisterStaged, TC, TP, 1, BKT, a.Cin % BKT != 0)) return DAT_OK;
   const int npt8 = (a.npt + 7) / 8 * 8;
   if (a.Cin % BKT == 0 && a.Ktot > 0)
     hipLaunchKernelGGL((igemm_kernel<TC, TP, WGC, PF, true, BKT, OCC>), dim3((unsigned)(npt8 * a.nct)), dim3(kThreads), 0, st, a);

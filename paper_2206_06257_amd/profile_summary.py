@@ -39,7 +39,7 @@ def _is_conv(n):
 
 
 TEMPLATES = [
-    "# Template arguments: igemm_dma_kernel<TC, TP, WGC, OCC, BK>, igemm_ring_kernel<TC, TP, WGC, S, NT, G, ANYC> (ANYC = true: k-tiles straddle filter taps),",
+    "# Template arguments: igemm_dma_kernel<TC, TP, WGC, OCC, BK, CL>, igemm_ring_kernel<TC, TP, WGC, S, NT, G, ANYC, CL> (ANYC = true: k-tiles straddle filter taps; CL: one launch or several classes in one),",
     "# igemm_kernel<TC, TP, WGC, PF, FAST, BK, OCC, XF> (XF = true: the operand is a BN input gradient formed while loading),",
     "# bnact_fwd_kernel<T, RES> (RES 0 none, 1 residual, 2 residual normalised on the fly), bnact_bwd_apply_kernel<T, GATE, DXACC, DRES>.",
 ]
