@@ -407,8 +407,9 @@ __global__ __launch_bounds__(kThreads, OCC) void igemm_kernel(IgemmArgs a) {
     nb[i] = n * a.Hin * a.Win;
   }
   const int ntiles = (a.Ktot + BKT - 1) / BKT;
+  // (the symbol itself, not a pointer hidden from the compiler: it must see that both sides of the selects below are global
+  // memory, or the loads become flat ones, which also count as LDS accesses: 1x1 256 -> 64 at 56x56, 256 images 94 us, flat 101)
   const u32x4* zero_page = reinterpret_cast<const u32x4*>(g_zero_page);
-  asm("" : "+s"(zero_page));     // (kept in registers: the compiler would load the symbol's address again in every k-tile)
 
   // Weight rows of this thread: offset of (row, k = kvec*8) and row validity; advances by BK per tile.
   int woff[VW]; bool wrow[VW];
@@ -465,7 +466,7 @@ __global__ __launch_bounds__(kThreads, OCC) void igemm_kernel(IgemmArgs a) {
         if (XF) {
           const u32x4* py = ok ? reinterpret_cast<const u32x4*>(a.xf_x + xoff[i]) : zero_page;
           r.y[i] = *py;
-          const uint8_t* pm = (ok && a.xf_mask) ? a.xf_mask + (xoff[i] >> 3) : reinterpret_cast<const uint8_t*>(zero_page);
+          const uint8_t* pm = (ok && a.xf_mask) ? a.xf_mask + (xoff[i] >> 3) : reinterpret_cast<const uint8_t*>(g_zero_page);
           r.mk[i] = a.xf_mask ? (uint32_t)*pm : (ok ? 0xffu : 0u);
         }
         xoff[i] += BKT;
