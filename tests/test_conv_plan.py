@@ -52,3 +52,9 @@ def test_slabs_written_are_the_slabs_read_while_a_switch_changes():
             t.join()
         sys.setswitchinterval(interval)
     assert tiles == {128, 256} and bad == 0
+
+
+@pytest.mark.parametrize("shape", [(16, 14, 14, 64, 160, 1, 1, 0), (128, 14, 14, 192, 160, 1, 1, 0), (16, 14, 14, 128, 480, 1, 1, 0), (128, 14, 14, 64, 320, 1, 1, 0)])
+def test_short_contractions_into_multiples_of_160_go_direct_to_lds(shape):
+    p = dat.conv_plan(shape)
+    assert (p["kernel"], p["tile_c"], p["tile_p"], p["k_tile"]) == (1, 160, 128, 64)

@@ -44,6 +44,7 @@ SHAPES = [
     (5, 9, 11, 160, 160, 3, 1, 1),     # 160-channel tiles with a ragged pixel tail
     (2, 8, 8, 96, 160, 3, 1, 1),       # k-tiles of 64 over 96-channel taps: a tile ends two thirds into a tap
     (2, 9, 9, 32, 160, 5, 1, 2),       # ... and two taps per k-tile (5x5 window)
+    (3, 11, 7, 192, 480, 1, 1, 0),     # 160-channel tiles, a contraction of three 64-wide k-tiles
     (8, 4, 4, 512, 512, 3, 1, 1),      # last stage of the CIFAR ResNets: few tiles, long contraction
     (2, 8, 8, 1024, 256, 1, 1, 0),     # reducing 1x1 layer with a long contraction
 ]
