@@ -186,6 +186,9 @@ WGRAD_SHAPES = [
     (60, 28, 28, 128, 64, 1, 1, 0),    # narrow 1x1
     (999, 3, 3, 256, 256, 3, 2, 1),    # 2x2 outputs: 16 images in a tile, ragged end
     (700, 5, 5, 64, 200, 3, 1, 1),     # a tile ends inside an image of 25 pixels
+    (512, 8, 8, 256, 512, 1, 2, 0),    # 4x4 outputs: four whole images per tile
+    (130, 7, 9, 64, 72, 3, 1, 1),      # 63 pixels per image: a tile is one image and one pixel
+    (350, 2, 3, 64, 136, 3, 1, 1),     # six pixels per image: ten images, one row and one column per tile
     (3, 65, 67, 40, 64, 5, 1, 2),      # rows longer than a tile, 5x5 window, channels that are no power of two
 ]
 
