@@ -1581,11 +1581,18 @@ WgradPlan plan_wgrad(const ConvGeom& g) {
   if (pieces > max_by_pixels) pieces = max_by_pixels;
   if (pieces > 512) pieces = 512;
   p.chunk = ((M + pieces - 1) / pieces + 63) / 64 * 64;
-  // splits: one round of workgroups.  Two per CU; three of the narrow tiles of a filter window (56x56 64 -> 64 at 256
-  // images 92 us, two 95; the 1x1 layers are bound by HBM and the partial tiles count: 95.7, three 100.7), each at least
-  // five tiles long (50 images of 10x10, 256 -> 256 26.5, with four tiles 28)
-  int splits = (p.narrow && g.k > 1 ? 3 : 2) * compute_units() / tiles;
-  if (splits > (M + 319) / 320) splits = (M + 319) / 320;
+  // splits: one round of workgroups, each at least five tiles long (four tiles: 18 of 558 measured shapes 4 to 19 % slower, 14x14
+  // 1024 -> 256, 21 images 20.5 us, with four 24.5).  Two workgroups per CU; three of the narrow tiles of a filter window (64 -> 64
+  // at 56x56, 256 images 92 us, two 95; but at 32x32, 391 images 57.9, two 57.1, and 40x40, 50 images 23.6, two 22.9; the 1x1
+  // layers are bound by HBM and the partial tiles count: 95.7, three 100.7).  Where five tiles each leave less than that
+  // round, some CUs hold one workgroup and some two: one for each then, longer, with fewer partial tiles (128 -> 256 / 2 into
+  // 8x8, 100 images 360 workgroups 27.5 us, 252 23.4; 1x1 320 -> 640 / 2 into 8x8 24.6, 22.9; none of the 558 slower).
+  const int cus = compute_units();
+  int splits = (p.narrow && g.k > 1 ? 3 : 2) * cus / tiles;
+  if (splits > (M + 319) / 320) {
+    splits = (M + 319) / 320;
+    if (splits * tiles <= 2 * cus && splits > cus / tiles && cus >= tiles) splits = cus / tiles;
+  }
   if (splits < 1) splits = 1;
   const int span = (int)((int64_t)M * g.Cout >> 29) + 1;         // a split's dY stays below 2 GiB: 32-bit offsets past its end
   if (splits < span) splits = span;
