@@ -58,3 +58,18 @@ def test_slabs_written_are_the_slabs_read_while_a_switch_changes():
 def test_short_contractions_into_multiples_of_160_go_direct_to_lds(shape):
     p = dat.conv_plan(shape)
     assert (p["kernel"], p["tile_c"], p["tile_p"], p["k_tile"]) == (1, 160, 128, 64)
+
+
+def test_multi_stage_shapes_of_the_gpu_tests_reach_every_configuration():
+    """The list that tests/test_gpu_conv.py runs: each shape gets the tiles it is there for, and together they reach every
+    tile of the multi-stage kernel, ordinary launches and launches in parity classes."""
+    from tests.test_gpu_conv import RING_SHAPES
+    reached = set()
+    for shape, forward, backward in RING_SHAPES:
+        for p, want in ((dat.conv_plan(shape), forward), (dat.conv_plan(shape, True), backward)):
+            assert (p["kernel"], p["tile_c"], p["tile_p"], p["straddle"], p["classes"]) == want, (shape, p)
+            if p["kernel"] == 2:
+                reached.add(want[1:])
+    ordinary = {(32, 128, 0), (64, 128, 0), (128, 128, 0), (256, 128, 0), (256, 256, 0), (160, 128, 0), (160, 256, 0), (160, 128, 1), (160, 256, 1)}
+    classes = {(32, 128, 0), (64, 128, 0), (128, 128, 0), (160, 128, 0), (160, 128, 1)}
+    assert reached == {t + (0,) for t in ordinary} | {t + (4,) for t in classes}

@@ -2,6 +2,8 @@
 convolution, per layer shape (bf16 operands, fp32 accumulate): the inputs are bf16 values, so
 the exact result is the fp64 sum; the kernel may differ from it by fp32 accumulation error
 before its single rounding to bf16."""
+import contextlib
+
 import numpy as np
 import pytest
 import torch
@@ -92,90 +94,117 @@ def test_conv_forward_backward_parity(dat, shape):
 
 
 
-# long contractions into more than 64 channels: at these sizes they have few tiles and run in 32-channel tiles
-FEW_TILE_SHAPES = [s for s in SHAPES if s[3] % 64 == 0 and s[4] > 64 and s[5] * s[5] * s[3] >= 1024]
-
-
-def _ab(dat, shape, option, what):
-    B, H, W, Ci, Co, k, st, pad = shape
-    rng = np.random.default_rng(hash(shape) % (2 ** 31) + 1)
-    x = _bf16_values(rng, (B, H, W, Ci)).cuda()
-    w = _bf16_values(rng, (Co, k, k, Ci), 1.0 / np.sqrt(Ci * k * k)).cuda()
-    Ho, Wo = (H + 2 * pad - k) // st + 1, (W + 2 * pad - k) // st + 1
-    dy = _bf16_values(rng, (B, Ho, Wo, Co)).cuda()
-    res = []
+@contextlib.contextmanager
+def _switches(dat, value):
+    """All three kernel switches: with all of them off every layer runs in the single-stage and register-staged kernels, none
+    in 160-channel tiles (one off alone leaves the others' tiles)."""
+    options = (dat.KOPT_RING_KERNEL, dat.KOPT_TILE_160, dat.KOPT_NARROW_UNDERFILLED)
     try:
-        for on in (1, 0):
-            dat.set_kernel_option(option, on)
-            y = dat.conv_forward(x, w, st, pad)
-            dx = dat.conv_backward_data(dy, w, (H, W), st, pad)
-            torch.cuda.synchronize()
-            res.append((y.view(torch.int16).cpu().numpy(), dx.view(torch.int16).cpu().numpy()))
+        for o in options:
+            dat.set_kernel_option(o, value)
+        yield
     finally:
-        dat.set_kernel_option(option, 1)
-    _check(y, oracle.conv_forward(x.double().cpu().numpy(), w.double().cpu().numpy(), st, pad), "forward, " + what)
-    _check(dx, oracle.conv_backward(x.double().cpu().numpy(), w.double().cpu().numpy(), dy.double().cpu().numpy(), st, pad)[0],
-           "backward_data, " + what)
-    assert np.array_equal(res[0][0], res[1][0]) and np.array_equal(res[0][1], res[1][1])
+        for o in options:
+            dat.set_kernel_option(o, 1)
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+def test_single_stage_kernels_parity(dat, shape):
+    """The kernels that larger layers of these kinds run in, held to the oracle at the same small sizes (by themselves the
+    sizes have few tiles, and most of them choose the multi-stage kernel)."""
+    B, H, W, Ci, Co, k, st, pad = shape
+    rng = np.random.default_rng(hash(shape) % (2 ** 31) + 2)
+    x, w = _bf16_values(rng, (B, H, W, Ci)), _bf16_values(rng, (Co, k, k, Ci), 1.0 / np.sqrt(Ci * k * k))
+    x64, w64 = x.double().numpy(), w.double().numpy()
+    y64 = oracle.conv_forward(x64, w64, st, pad)
+    dy = _bf16_values(rng, y64.shape)
+    with _switches(dat, 0):
+        for backward in (False, True):
+            p = dat.conv_plan(shape, backward)
+            assert p["kernel"] < 2 and p["tile_c"] != 160
+        _check(dat.conv_forward(x.cuda(), w.cuda(), st, pad), y64, "forward")
+        _check(dat.conv_backward_data(dy.cuda(), w.cuda(), (H, W), st, pad), oracle.conv_backward(x64, w64, dy.double().numpy(), st, pad)[0],
+               "backward_data")
+
+
+# long contractions into more than 64 channels: at these sizes they have few tiles and run in 32-channel tiles
+FEW_TILE_SHAPES = [s for s in SHAPES if s[3] % 64 == 0 and s[4] > 64 and s[4] % 160 != 0 and s[5] * s[5] * s[3] >= 1024]
+
+
+def _ab(dat, shape):
+    """Forward and backward-data with the switches on and off."""
+    B, H, W, Ci, Co, k, st, pad = shape
+    g = torch.Generator(device="cuda").manual_seed(B * H + Co)
+    Ho, Wo = (H + 2 * pad - k) // st + 1, (W + 2 * pad - k) // st + 1
+    x, w, dy = (torch.randn(*s, device="cuda", generator=g).to(torch.bfloat16) for s in ((B, H, W, Ci), (Co, k, k, Ci), (B, Ho, Wo, Co)))
+    res = []
+    for on in (1, 0):
+        with _switches(dat, on):
+            res.append((dat.conv_forward(x, w, st, pad), dat.conv_backward_data(dy, w, (H, W), st, pad)))
+            torch.cuda.synchronize()
+    for a, b in zip(*res):
+        assert torch.isfinite(a.float()).all() and a.float().abs().max() > 0
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16))
 
 
 @pytest.mark.parametrize("shape", WIDE_NET_SHAPES)
 def test_160_channel_tiles_give_the_bits_of_128_channel_tiles(dat, shape):
     """Layers 160 or 320 channels wide run in 160-channel tiles (no partly empty last tile).  Every output element is
     the same chain of MFMA accumulations over the same k order under either tiling, so forward and backward-data
-    results must not differ by a bit; the 128-channel launches stay covered by this test."""
-    _ab(dat, shape, dat.KOPT_TILE_160, "128-channel tiles")
+    results must not differ by a bit from those of the 128-channel tiles."""
+    for backward, width in ((False, shape[4]), (True, shape[3])):
+        assert (dat.conv_plan(shape, backward)["tile_c"] == 160) == (width in (160, 320))
+    _ab(dat, shape)
 
 
 @pytest.mark.parametrize("shape", FEW_TILE_SHAPES)
 def test_32_channel_tiles_of_underfilled_layers_give_the_bits_of_128_channel_tiles(dat, shape):
-    """A long contraction with too few 128x128 tiles to keep the compute units busy runs in 32-channel tiles.  Same k order
-    per accumulator, so the same bits; with the switch off these shapes go through the 128-channel kernels, which this
-    test thereby keeps covered at small sizes."""
-    assert len(FEW_TILE_SHAPES) >= 6
-    _ab(dat, shape, dat.KOPT_NARROW_UNDERFILLED, "128-channel tiles")
+    """A long contraction with too few 128x128 tiles to keep the compute units busy runs in 32-channel tiles of the multi-stage
+    kernel.  Same k order per accumulator, so the same bits as the 128-channel tiles of the single-stage kernel."""
+    assert len(FEW_TILE_SHAPES) >= 5
+    p = dat.conv_plan(shape)
+    assert (p["kernel"], p["tile_c"]) == (2, 32)
+    with _switches(dat, 0):
+        p = dat.conv_plan(shape)
+        assert (p["kernel"], p["tile_c"]) == (1, 128)
+    _ab(dat, shape)
 
 
-# One shape for every tile configuration of the multi-stage kernel (256 compute units), with ragged pixel and channel tails:
-# the number of tiles decides which one a layer gets, so these have as many pixels as that takes.
+# One shape for every tile configuration of the multi-stage kernel, with ragged pixel and channel tails: the number of tiles
+# decides which one a layer gets (256 compute units), so these have as many pixels as that takes.  After the shape: (kernel,
+# tile channels, tile pixels, k-tiles straddle taps, classes) of the forward and of the backward-data pass, kernel 2 being
+# the multi-stage one.
 RING_SHAPES = [
-    (13, 4, 4, 512, 200, 3, 1, 1),     # 32-channel tiles: few tiles
-    (1, 3, 3, 256, 40, 1, 1, 0),       # ... fewer k-tiles than pipeline stages + 1, one pixel tile, <= 64 channels
-    (11, 28, 28, 64, 72, 3, 1, 1),     # 64-channel tiles (68 128-pixel tiles)
-    (21, 28, 28, 64, 104, 3, 1, 1),    # 128-channel tiles, 8 waves (129)
-    (21, 29, 29, 64, 128, 3, 2, 1),    # ... odd strided layer: four parity classes in backward-data
-    (21, 28, 28, 128, 256, 3, 1, 1),   # 256 channels x 128 pixels (129)
-    (40, 31, 31, 128, 256, 3, 1, 1),   # 256 x 256 (151)
-    (5, 15, 15, 64, 160, 3, 1, 1),     # 160 x 128, one tile per compute unit
-    (5, 61, 61, 64, 320, 3, 1, 1),     # 160 x 256 (146 x 2: two 128-pixel tiles per compute unit)
-    (9, 61, 61, 160, 160, 3, 1, 1),    # ... with k-tiles that straddle the filter taps
-    (17, 61, 61, 96, 160, 3, 1, 1),    # 160 x 128 likewise, an odd number of tiles per compute unit's share
-    (7, 30, 30, 320, 640, 1, 2, 0),    # 640 channels
+    ((13, 4, 4, 512, 200, 3, 1, 1), (2, 32, 128, 0, 0), (0, 128, 128, 1, 0)),      # few tiles
+    ((1, 3, 3, 256, 40, 1, 1, 0), (2, 32, 128, 0, 0), (0, 128, 128, 1, 0)),        # ... fewer k-tiles than stages + 1, one pixel tile
+    ((11, 28, 28, 64, 72, 3, 1, 1), (2, 64, 128, 0, 0), (0, 64, 128, 1, 0)),       # 68 128-pixel tiles
+    ((11, 28, 28, 128, 128, 3, 1, 1), (2, 64, 128, 0, 0), (2, 64, 128, 0, 0)),
+    ((21, 28, 28, 64, 104, 3, 1, 1), (2, 128, 128, 0, 0), (0, 64, 128, 1, 0)),     # 129
+    ((11, 28, 28, 136, 128, 3, 1, 1), (0, 128, 128, 1, 0), (2, 128, 128, 0, 0)),   # 68 x 2, the second channel tile almost empty
+    ((21, 28, 28, 128, 256, 3, 1, 1), (2, 256, 128, 0, 0), (2, 128, 128, 0, 0)),   # 129
+    ((42, 31, 31, 256, 256, 3, 1, 1), (2, 256, 256, 0, 0), (2, 256, 256, 0, 0)),   # 158 256-pixel tiles, the last one two thirds full
+    ((3, 29, 29, 72, 64, 3, 2, 1), (0, 64, 128, 1, 0), (2, 32, 128, 0, 4)),        # odd strided layers: parity classes of 225 to 196
+    ((11, 29, 29, 72, 64, 3, 2, 1), (0, 64, 128, 1, 0), (2, 64, 128, 0, 4)),       # pixels per image, 21, 75 and 140 tiles
+    ((21, 29, 29, 72, 64, 3, 2, 1), (0, 64, 128, 1, 0), (2, 128, 128, 0, 4)),
+    ((3, 17, 17, 160, 96, 5, 2, 2), (0, 128, 128, 0, 0), (2, 160, 128, 1, 4)),      # ... with k-tiles that straddle the filter taps
+    ((5, 15, 15, 64, 160, 3, 1, 1), (2, 160, 128, 0, 0), (1, 64, 128, 0, 0)),      # one 128-pixel tile per compute unit
+    ((5, 30, 30, 64, 640, 3, 1, 1), (2, 160, 128, 0, 0), (2, 32, 128, 0, 0)),
+    ((12, 61, 61, 64, 320, 3, 1, 1), (2, 160, 128, 0, 0), (1, 64, 128, 0, 0)),     # three (349 x 2)
+    ((5, 61, 61, 64, 320, 3, 1, 1), (2, 160, 256, 0, 0), (1, 64, 128, 0, 0)),      # two (146 x 2)
+    ((9, 61, 61, 160, 160, 3, 1, 1), (2, 160, 256, 1, 0), (2, 160, 256, 1, 0)),    # ... with k-tiles that straddle the filter taps
+    ((17, 61, 61, 96, 160, 3, 1, 1), (2, 160, 256, 1, 0), (0, 128, 128, 0, 0)),
+    ((5, 61, 61, 96, 160, 3, 1, 1), (2, 160, 128, 1, 0), (0, 128, 128, 0, 0)),     # one (146)
+    ((7, 30, 30, 320, 640, 1, 2, 0), (2, 64, 128, 0, 0), (2, 160, 128, 0, 4)),     # 640 channels, 13 tiles
 ]
 
 
-@pytest.mark.parametrize("shape", RING_SHAPES)
-def test_multi_stage_tiles_give_the_bits_of_the_single_stage_kernels(dat, shape):
+@pytest.mark.parametrize("shape,forward,backward", RING_SHAPES)
+def test_multi_stage_tiles_give_the_bits_of_the_single_stage_kernels(dat, shape, forward, backward):
     """Every output is the same chain of MFMA accumulations in every tile configuration; with the three switches off the same
-    layers run in the single-stage kernels that the tests above hold to the oracle."""
-    B, H, W, Ci, Co, k, st, pad = shape
-    g = torch.Generator(device="cuda").manual_seed(B * H + Co)
-    Ho, Wo = (H + 2 * pad - k) // st + 1, (W + 2 * pad - k) // st + 1
-    x, w, dy = (torch.randn(*s, device="cuda", generator=g).to(torch.bfloat16) for s in ((B, H, W, Ci), (Co, k, k, Ci), (B, Ho, Wo, Co)))
-    options = (dat.KOPT_RING_KERNEL, dat.KOPT_TILE_160, dat.KOPT_NARROW_UNDERFILLED)
-    res = []
-    try:
-        for on in (1, 0):
-            for o in options:
-                dat.set_kernel_option(o, on)
-            res.append((dat.conv_forward(x, w, st, pad), dat.conv_backward_data(dy, w, (H, W), st, pad)))
-            torch.cuda.synchronize()
-    finally:
-        for o in options:
-            dat.set_kernel_option(o, 1)
-    for a, b in zip(*res):
-        assert torch.isfinite(a.float()).all() and a.float().abs().max() > 0
-        assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+    layers run in the kernels that test_single_stage_kernels_parity holds to the oracle."""
+    for p, want in ((dat.conv_plan(shape), forward), (dat.conv_plan(shape, True), backward)):
+        assert (p["kernel"], p["tile_c"], p["tile_p"], p["straddle"], p["classes"]) == want
+    _ab(dat, shape)
 
 
 # pixel ranges of several chains of sums, few (<= 16) and many of them, both tile widths, images smaller than a tile
