@@ -256,9 +256,11 @@ dat_status dat_conv_backward_weight(const uint16_t* x, const uint16_t* dy, float
  * dat_conv_backward_weight keeps in a workspace allocated per call, go to a buffer of
  * dat_conv_backward_weight_static_limit() = 32 MiB that is part of the library's device image (each GPU the
  * library runs on holds it until the process ends).  Same arguments, same kernels, same bits as
- * dat_conv_backward_weight.  Returns DAT_ERR_UNSUPPORTED (text in dat_last_error) when the shape's partial sums
- * (chains * Cout*k*k*Cin * 4 bytes; the count of chains, ranges of at least 256 output pixels summed in fp32, grows
- * with B*Ho*Wo up to 2048 over the output tiles) do not fit, and launches nothing then.
+ * dat_conv_backward_weight.  Which shapes it takes is fixed, and more than what a call stores: with M = B*Ho*Wo output
+ * pixels, t = ceil(Cout / 128 (64 if Cout <= 64)) * ceil(k*k*Cin / 128) output tiles, n = min(ceil(2048 / t),
+ * ceil(M / 256), 512) and c = ceil(M / n) rounded up to a multiple of 64 (the length of a chain of fp32 sums),
+ * ceil(M / c) * Cout*k*k*Cin * 4 bytes must fit into the buffer: one partial sum per chain, where a call stores one per
+ * range of several chains.  Otherwise it returns DAT_ERR_UNSUPPORTED (text in dat_last_error) and launches nothing.
  * All calls on one GPU share that buffer: calls that overlap in time on one GPU (different streams or threads)
  * race; calls on one stream are ordered and safe.  Nothing in the buffer needs clearing between calls: every
  * partial sum a call reads was written by its own first launch. */

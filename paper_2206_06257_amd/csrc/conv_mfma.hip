@@ -1955,12 +1955,13 @@ extern "C" dat_status dat_conv_backward_weight_static(const uint16_t* x, const u
   ConvGeom g;
   if (!x || !dy || !dw || !geom_from(B, H, W, Cin, Cout, k, stride, pad, &g)) return DAT_ERR_ARG;
   if (!aligned(x, 16) || !aligned(dy, 16) || !aligned(dw, 16)) return DAT_ERR_ARG;
-  // (the limit counts one partial tile per chain of sums, which the pixel ranges of a call never outnumber by much)
+  // (the limit counts one partial sum per chain, as if each were stored: the shapes this entry point takes do not depend on how
+  // many chains a workgroup adds up before it stores, nor on the number of compute units)
   const WgradPlan p = plan_wgrad(g);
   const size_t tile_bytes = (size_t)Cout * k * k * Cin * sizeof(float), chains = ((size_t)B * g.Ho * g.Wo + p.chunk - 1) / p.chunk;
   if (chains * tile_bytes > (size_t)DAT_STATIC_SCRATCH_BYTES || conv_mfma_wgrad_workspace(g) > (size_t)DAT_STATIC_SCRATCH_BYTES)
-    return fail_with(DAT_ERR_UNSUPPORTED, "dat_conv_backward_weight_static: the split partial sums of this shape exceed the 32 MiB static scratch "
-                                          "(use dat_conv_backward_weight)");
+    return fail_with(DAT_ERR_UNSUPPORTED, "dat_conv_backward_weight_static: one partial sum for each chain of this shape exceeds the 32 MiB static "
+                                          "scratch (use dat_conv_backward_weight)");
   void* ws = nullptr;
   const dat_status s = static_scratch(&ws);
   if (s != DAT_OK) return s;

@@ -27,11 +27,11 @@ def _case(dat, B, H, Cin, Cout, k, stride, pad, seed):
 
 
 def test_static_scratch_entry_point_matches_the_allocating_one(dat):
-    # first call: 25 splits of a 128 x 1152 tile set (14.7 MB of partial sums)
+    # first call: 20 pixel ranges of a 128 x 1152 tile set (11.8 MB of partial sums)
     want, got = _case(dat, 8, 28, 128, 128, 3, 1, 1, seed=1)
     assert np.isfinite(got).all() and np.abs(want).max() > 0
     assert np.array_equal(got, want)
-    # second call, smaller input: fewer splits, fewer columns -- the first call's partial sums are still in the buffer
+    # second call, smaller input: fewer ranges, fewer columns -- the first call's partial sums are still in the buffer
     want2, got2 = _case(dat, 3, 14, 64, 72, 3, 2, 1, seed=2)
     assert np.isfinite(got2).all() and np.abs(want2).max() > 0
     assert np.array_equal(got2, want2)
