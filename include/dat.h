@@ -337,8 +337,9 @@ typedef enum { DAT_OPT_FUSE_BN_INPUT_GRAD = 0, DAT_OPT_FUSE_BN_SUMS = 1, DAT_OPT
                DAT_OPT_KEEP_BOTH_PASSES = 8 } dat_option;
 dat_status dat_model_set_option(dat_model* m, dat_option opt, int value);
 /* Process-wide kernel selection (ablations and tests; atomic flags, read once per convolution of every
- * model and of the dat_conv_* entry points).  With an option off its layers run in 128-channel tiles of the
- * single-stage kernels; the convolution outputs are bit-identical, the grouping of the batch-norm partial sums differs.
+ * model and of the dat_conv_* entry points).  The options are independent: with one off its layers run as
+ * the other rules have it; with all off every layer runs in the single-stage and register-staged kernels, in tiles of at most
+ * 128 channels.  The convolution outputs are bit-identical, the grouping of the batch-norm partial sums differs.
  * DAT_KOPT_RING_KERNEL (default 1): long contractions that are one round of 256-channel tiles go through the
  * multi-stage kernel.
  * DAT_KOPT_TILE_160 (default 1): layers whose output channels are a multiple of 160 (the wide ResNets) run in

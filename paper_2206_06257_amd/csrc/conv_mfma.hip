@@ -17,21 +17,24 @@
 //   * `igemm_kernel` (any channel count, and the long 1x1 contractions into <= 64 channels):
 //     global -> registers -> LDS, double buffered, loads running PF k-tiles ahead.
 //   Backward-data is the same contraction over the output gradient: stride 1 with the flipped,
-//   transposed filter ([Cin][k][k][Cout]); stride 2 as four launches, one per parity class of the
-//   input pixels, each a dense stride-1 convolution with that class's sub-filter.
+//   transposed filter ([Cin][k][k][Cout]); stride 2 over the four parity classes of the input pixels,
+//   each a dense stride-1 convolution with that class's sub-filter, in one launch (four where the
+//   register-staged kernel runs).
 //   The shared epilogue adds an optional residual (or the previously stored gradient) in fp32,
 //   rounds once to bf16, transposes through LDS, writes 16-byte channel vectors and can emit the
 //   per-channel (sum, sum of squares) of what it stored: the batch statistics of the BN that follows.
 //   Workgroups are numbered so that the channel tiles of one pixel tile land on the same XCD
-//   (ids congruent mod 8 share an L2), which keeps the gathered activations L2-resident; layers
-//   with a filter window also give every XCD one contiguous range of pixel tiles, so that the
-//   rows neighbouring tiles share are re-read from that L2.
+//   (ids congruent mod 8 share an L2), which keeps the gathered activations L2-resident; in the
+//   single-stage and register-staged kernels, layers with a filter window also give every XCD one
+//   contiguous range of pixel tiles, so that the rows neighbouring tiles share are re-read from that L2.
+//   (Not in the multi-stage kernel, measured both ways: 0 to 2.5 % slower with it, 160 channels at 32x32,
+//   256 images 138.2 / 137.5 us, 640 at 8x8, 100 images 61.0 / 59.6, 256 at 14x14, 256 images 56.7 / 56.0.)
 //
 // Backward-weight (`wgrad_kernel`): dW[co][(r,s,ci)] = sum_p dY[p][co] * X[p][(r,s,ci)], a
 // contraction over pixels, which are the strided dimension of both operands.  The tiles land in
 // LDS as they are in memory ([pixel][channel], direct-to-LDS loads) and the MFMA fragments are
 // read with the LDS transpose reads of gfx950 (ds_read_b64_tr_b16), which hand every lane four
-// consecutive pixels of its channel.  The pixel range is split over gridDim.z; partial tiles go to a workspace
+// consecutive pixels of its channel.  The pixel range is split over workgroups; partial tiles go to a workspace
 // and a second kernel sums them in a fixed order (deterministic).
 #include <atomic>
 #include <mutex>
@@ -96,7 +99,7 @@ struct IgemmArgs {
   // layout as `out`), ReLU mask stat_mask (or nullptr) and batch statistics stat_mean / stat_rstd; the slabs then
   // hold (sum v*m, sum v*m*xhat), the two sums of that normalisation's backward pass.
   const bf16_t* stat_x; const uint8_t* stat_mask; const float* stat_mean; const float* stat_rstd;
-  // stat_mode 3 (128-channel tiles only): a second normalisation (input stat_x2, statistics stat_mean2 / stat_rstd2)
+  // stat_mode 3 (results with more than 64 channels only): a second normalisation (input stat_x2, statistics stat_mean2 / stat_rstd2)
   // shares that output gradient; slabs are [3][Cout]: (sum v*m, sum v*m*xhat, sum v*m*xhat2).
   const bf16_t* stat_x2; const float* stat_mean2; const float* stat_rstd2;
   // Optional operand transform (1x1 stride-1 layers, igemm_kernel only): `in` is the output gradient of a batch
@@ -110,7 +113,8 @@ struct IgemmArgs {
 
 // Several launches of one kernel as one grid: what differs between them.  The four parity classes of a stride-2
 // backward-data pass go this way, the classes with most taps first (their workgroups run longest).  Each class has
-// blocks [begin, next begin), a multiple of 8, so the tile numbering inside a class is that of a launch of its own.
+// blocks [begin, next begin), a multiple of 8, so a class's tiles meet the XCDs as in a launch of its own (whether
+// interleaved or in ranges, xcd_contiguous, is decided for all classes by the one with most taps).
 struct IgemmClass { const bf16_t* wt; int Hout, Wout, KH, KW, pad_h, pad_w, oh0, ow0, M, Ktot, stat_slab0, with_res, npt, begin; };
 struct IgemmClasses { int n; IgemmClass c[4]; };
 // An ordinary launch: a kernel of its own, without the table.  With the table as an argument of every launch and all four
@@ -591,7 +595,7 @@ __global__ __launch_bounds__(kThreads, OCC) void igemm_kernel(IgemmArgs a) {
 }
 
 // ---- direct-to-LDS variant (contraction channels a multiple of 64) ---------------------------------
-// Operand tiles go from global memory straight into LDS (global_load_lds_dwordx4: every lane names
+// Operand tiles go from global memory straight into LDS (buffer_load_dwordx4 ... lds: every lane names
 // its own 16-byte source, the 64 vectors of a wave land contiguously at a wave-uniform LDS address):
 // no staging registers and no ds_write, so four workgroups stay resident per CU with 64-wide k-tiles,
 // whose 128-byte rows use whole cache lines (the vector L1 moves ~0.45 lines per clock whether a wave
@@ -600,9 +604,7 @@ __global__ __launch_bounds__(kThreads, OCC) void igemm_kernel(IgemmArgs a) {
 // The XOR swizzle of the 16-byte slots is applied on the source side: the lane that fills physical
 // slot p of a row fetches logical k-slot p ^ f(row).
 typedef __attribute__((address_space(3))) void* lds_void_ptr;
-typedef const __attribute__((address_space(1))) void* gbl_void_ptr;
 
-//
 // The loads go through buffer descriptors (buffer_load_dwordx4 ... lds): a lane's byte offset changes only with the
 // filter tap, the position inside the tap is the scalar offset of the instruction, and a vector outside the image or
 // the tensor carries the offset kOob, which lies beyond every descriptor's range: the hardware's range check then
@@ -1072,7 +1074,10 @@ Switches read_switches() {
 //  * at most one 128x128 tile per CU, contraction >= 256: the largest tile that still gives half of the CUs one.
 //    128x128 above half a tile per CU (20x20 128 -> 128 at 50 images 16.1 -> 12.4; 64x128 tiles 12.9), 64x128 above a
 //    quarter (10x10 256 -> 256 at 50 images 22.8 -> 15.4; 32x128 17.2, 128x128 19.1), else 32x128 (5x5 512 -> 512 at 50
-//    images 48.8 -> 19.6; 64x128 25.6).
+//    images 48.8 -> 19.6; 64x128 25.6).  The line is at one tile per CU: between 1.0 and 1.5 the single-stage 128x128 kernel is
+//    ahead (16x16 128 -> 128 at 160 images 21.2, ring 128x128 25.1, 64x128 24.1, 32x128 28.2, single-stage 32x128 24.8; 28x28
+//    at 42 and 61 images 19.0 and 20.3, next best 22.1 and 22.8; the only tie 1x1 1024 -> 128 at 28x28, 60 images, 22.2, 64x128
+//    22.0).
 enum RingPick { kRNone, kR32, kR64, kR128, kR256x128, kR256x256, kR160x128, kR160x256, kR160x128Any, kR160x256Any };
 
 RingPick pick_ring(const IgemmArgs& a, const Switches& sw) {
@@ -1096,7 +1101,9 @@ RingPick pick_ring(const IgemmArgs& a, const Switches& sw) {
   }
   if (!sw.narrow) return kRNone;
   // A backward-data pass that igemm_kernel may also run with its operand transform (conv_mfma_bn_operand_ok) leaves its
-  // batch-norm sums in the same order either way: 64-channel tiles of 256 threads, or the 128-channel single-stage kernel.
+  // batch-norm sums in the same order either way: 64-channel tiles of 256 threads, or the 128-channel single-stage kernel
+  // (whose 128x128 tiles the 512-thread multi-stage ones would beat: 1x1 512 -> 128 at 28x28, 21 images 12.3 us, multi-stage 8.4;
+  // but a thread's rows there are others, and the two settings of the operand transform promise identical bits).
   if (a.stat_mode >= 2 && a.KH * a.KW == 1 && a.ostep == 1 && a.Cout > 32 && a.Cout <= 128 && a.Cin >= 2 * a.Cout)
     return a.Cout <= 64 && 2 * p128 <= cus ? kR64 : kRNone;
   const int64_t t = p128 * ((a.Cout + 127) / 128);
@@ -1113,7 +1120,7 @@ int pixel_tile(RingPick r) {
 dat_status run_igemm(const IgemmArgs& a, const Switches& sw, RingPick ring, hipStream_t st) {
   if (!t_record) g_launches.fetch_add(1, std::memory_order_relaxed);
   if (a.Cin % 8 != 0 || a.Cout % 8 != 0) return DAT_ERR_UNSUPPORTED;
-  if (a.stat_mode == 3 && (a.Cout <= 64 || a.xf_tab)) return DAT_ERR_UNSUPPORTED;   // three sums: 128-channel tiles only
+  if (a.stat_mode == 3 && (a.Cout <= 64 || a.xf_tab)) return DAT_ERR_UNSUPPORTED;   // three sums: the <= 64-channel kernels have no LDS for them
   if (a.xstride) {   // overlapping input pixels: the direct-to-LDS kernel with one tap per 64-wide k-tile
     if (a.Cout > 64 || a.xf_tab) return DAT_ERR_UNSUPPORTED;
     return a.Cout <= 32 ? launch_igemm_dma<32, 128, 1, 6>(a, st) : launch_igemm_dma<64, 128, 2, 5>(a, st);
@@ -1626,7 +1633,7 @@ int64_t conv_mfma_launch_count() { return g_launches.load(std::memory_order_rela
 constexpr int kPixelTile = 128;   // smallest TP of the configurations run_igemm selects (pixel_tile gives the one of a launch)
 
 int conv_stat_slabs(int64_t rows, int stride) {
-  // stride 2 backward-data runs four launches over the parity classes: at most 3 extra partial tiles
+  // stride 2 backward-data numbers its slabs by parity class: at most 3 extra partial tiles
   return (int)((rows + kPixelTile - 1) / kPixelTile) + (stride == 2 ? 4 : 0);
 }
 
@@ -1714,8 +1721,9 @@ dat_status conv_mfma_backward_data(const bf16_t* dy, const bf16_t* wT, bf16_t* d
   };
   if (n > 1) {
     // one launch: at 13 images of 32x32 four launches of a few workgroups each take about 8 us apiece, and in the larger
-    // layers every class had a last wave of its own (attack on the
-    // pre-activation ResNet-18, 13 images: 9.2 -> 8.4 ms; CIFAR ResNet-18, 512 images: 29.0 -> 27.6; WRN-34-10: 97.6 -> 95.8)
+    // layers every class had a last wave of its own (attacks, ms, four launches -> one: pre-activation ResNet-18, 13 images
+    // 9.23 -> 8.51; CIFAR ResNet-18, 512 images 28.01 -> 27.55; WRN-34-10, 256 images 95.1 -> 94.6; ResNet-50, 85 images
+    // 28.34 -> 28.08)
     IgemmClasses cl{};
     cl.n = n;
     for (int i = 0; i < n; ++i) cl.c[i] = cls[i];
