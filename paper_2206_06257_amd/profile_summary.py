@@ -62,10 +62,10 @@ def trace(d, prefix, workload, steps=2):
          "# (forward + backward-to-input + projected sign step) + outer forward/backward + 8-bit quantize/dequantize.  Durations in microseconds."]
     L += TEMPLATES
     L.append("# The backward-weight launches of the outer step run on a second stream (their durations overlap those of the main stream's kernels).")
-    L.append("%-62s %6s %12s %9s %6s %8s %8s" % ("kernel", "calls", "total_us", "avg_us", "pct", "min_us", "max_us"))
+    L.append("%-64s %6s %12s %9s %6s %8s %8s" % ("kernel", "calls", "total_us", "avg_us", "pct", "min_us", "max_us"))
     ig = [0, 0.0]
     for n, e in sorted(agg.items(), key=lambda kv: -kv[1][1]):
-        L.append("%-62s %6d %12.1f %9.2f %6.2f %8.1f %8.1f" % (n[:62], e[0], e[1], e[1] / e[0], 100 * e[1] / tot, e[2], e[3]))
+        L.append("%-64s %6d %12.1f %9.2f %6.2f %8.1f %8.1f" % (n[:64], e[0], e[1], e[1] / e[0], 100 * e[1] / tot, e[2], e[3]))
         if _is_conv(n):
             ig[0] += e[0]; ig[1] += e[1]
     L.append("")
@@ -105,7 +105,7 @@ def traffic(d, workload):
          "# calibration: a plain 1 GiB device copy (%s) reads FETCH_SIZE = %.0f KiB and WRITE_SIZE = %.0f KiB per dispatch -> scale factors %.3f (fetch), %.3f (write)"
          % (cal["FETCH_SIZE"][0][:40], cal["FETCH_SIZE"][1], cal["WRITE_SIZE"][1], ff, wf),
          "# one step = the attack iterations + outer step; MiB per launch after scaling",
-         "%-48s %6s %18s %18s %12s" % ("kernel", "calls", "fetch MiB/launch", "write MiB/launch", "total GiB")]
+         "%-64s %6s %18s %18s %12s" % ("kernel", "calls", "fetch MiB/launch", "write MiB/launch", "total GiB")]
     tot, ig, rows = 0.0, [0, 0.0, 0.0], []
     for n in f:
         fv, wv = f[n], w.get(n, [0.0] * len(f[n]))
@@ -115,7 +115,7 @@ def traffic(d, workload):
         if _is_conv(n):
             ig[0] += len(fv); ig[1] += sum(fv) * ff * 1024; ig[2] += sum(wv) * wf * 1024
     for t, n, c, fm, wm in sorted(rows, reverse=True):
-        L.append("%-48s %6d %18.1f %18.1f %12.2f" % (n[:48], c, fm, wm, t / 1024))
+        L.append("%-64s %6d %18.1f %18.1f %12.2f" % (n[:64], c, fm, wm, t / 1024))
     L.append("")
     L.append("whole step: %.1f GiB of HBM traffic (%.0f ms at the nominal 8 TB/s)" % (tot / 1024, tot * 1048576 / 8.0e12 * 1e3))
     L.append("conv forward + backward-data kernels (without the <..., true> instantiations that also form a BN input gradient): %d launches, "
@@ -148,7 +148,7 @@ def mfma(d, prefix, workload):
          "#   every v_mfma_f32_32x32x16_bf16 keeps its SIMD's matrix unit busy for 32 cycles.",
          "# TFLOP/s(mfma) = SQ_INSTS_MFMA x 32768 FLOP / launch time (counts the padded tiles: an upper bound of the algorithmic rate).",
          "# wait = SQ_WAIT_INST_ANY / SQ_WAVE_CYCLES: share of a resident wave's cycles spent waiting on an instruction counter.",
-         "%-50s %9s %5s %9s %11s %9s %6s %9s" % ("kernel", "grid", "calls", "avg_us", "mfma_insts", "TFLOP/s", "wait", "mfma_busy")]
+         "%-64s %9s %5s %9s %11s %9s %6s %9s" % ("kernel", "grid", "calls", "avg_us", "mfma_insts", "TFLOP/s", "wait", "mfma_busy")]
     rows = []
     for k, e in agg.items():
         if not k[0].startswith(("igemm", "wgrad_kernel")) or not e["_n"]:
@@ -157,7 +157,7 @@ def mfma(d, prefix, workload):
         rows.append((e["_t"], k, n, e["_t"] / n / 1e3, e["SQ_INSTS_MFMA"] / n, e["SQ_INSTS_MFMA"] * 32768 / (e["_t"] * 1e-9) / 1e12,
                      e["SQ_WAIT_INST_ANY"] / max(e["SQ_WAVE_CYCLES"], 1), e["SQ_VALU_MFMA_BUSY_CYCLES"] / max(32 * e["SQ_BUSY_CYCLES"], 1)))
     for t, k, n, us, mi, tf, wa, mb in sorted(rows, reverse=True):
-        L.append("%-50s %9d %5d %9.1f %11.0f %9.0f %6.2f %9.3f" % (k[0][:50], k[1], n, us, mi, tf, wa, mb))
+        L.append("%-64s %9d %5d %9.1f %11.0f %9.0f %6.2f %9.3f" % (k[0][:64], k[1], n, us, mi, tf, wa, mb))
     ig = [r for r in rows if r[1][0].startswith("igemm")]
     num = sum(agg[r[1]]["SQ_VALU_MFMA_BUSY_CYCLES"] for r in ig); den = sum(32 * agg[r[1]]["SQ_BUSY_CYCLES"] for r in ig)
     L.append("")
