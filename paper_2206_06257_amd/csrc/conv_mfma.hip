@@ -1069,7 +1069,9 @@ Switches read_switches() {
 //    per CU at a time, or two 128-pixel ones; the same work per round, the larger tile 2-5 % faster (640 channels, 256
 //    images 99.7 / 106.7).  With an odd number of 128-pixel tiles per CU the larger tile would leave half of its last
 //    round idle (640 channels, 128 images, one tile per CU: 72 / 63).
-//  * kR256x256, kR256x128: contraction >= 1024 into a multiple of 256 channels, one round over at least 60 (50) % of the CUs:
+//  * kR256x256, kR256x128: contraction >= 1024 into a multiple of 256 channels, one round over at least 60 % (more than half)
+//    of the CUs.  (On exactly half of them the 128x128 tiles below are one full round: 4x4 512 -> 512 at 512 images 50.8, 128x128
+//    37.4; 8x8 256 -> 256 at 256 images 29.0, 22.0; 1x1 2048 -> 512 at 8x8, 128 images 27.9, 21.0.)
 //    14x14 256 -> 256 at 256 images 65 (128x128 tiles) -> 56, 7x7 512 -> 512 75 -> 58; 14x14 at 85 images (131 tiles) 40 -> 28.
 //  * at most one 128x128 tile per CU, contraction >= 256: the largest tile that still gives half of the CUs one.
 //    128x128 above half a tile per CU (20x20 128 -> 128 at 50 images 16.1 -> 12.4; 64x128 tiles 12.9), 64x128 above a
@@ -1097,7 +1099,7 @@ RingPick pick_ring(const IgemmArgs& a, const Switches& sw) {
   if (one_grid && a.Ktot >= 1024 && a.Cout % 256 == 0 && sw.ring) {
     const int64_t nct = a.Cout / 256, t256 = p256 * nct, t128 = p128 * nct;
     if (t256 <= cus && 5 * t256 >= 3 * cus) return kR256x256;
-    if (t128 <= cus && 2 * t128 >= cus) return kR256x128;
+    if (t128 <= cus && 2 * t128 > cus) return kR256x128;
   }
   if (!sw.narrow) return kRNone;
   // A backward-data pass that igemm_kernel may also run with its operand transform (conv_mfma_bn_operand_ok) leaves its

@@ -54,6 +54,15 @@ def test_slabs_written_are_the_slabs_read_while_a_switch_changes():
     assert tiles == {128, 256} and bad == 0
 
 
+@pytest.mark.parametrize("shape,tile_c", [
+    ((512, 4, 4, 512, 512, 3, 1, 1), 128), ((256, 8, 8, 256, 256, 3, 1, 1), 128),   # 256 128x128 tiles: one full round
+    ((513, 4, 4, 512, 512, 3, 1, 1), 256), ((257, 8, 8, 256, 256, 3, 1, 1), 256),   # one more: 130 and 129 256x128 tiles
+])
+def test_256_channel_tiles_start_where_128_channel_tiles_need_a_second_round(shape, tile_c):
+    for p in (dat.conv_plan(shape), dat.conv_plan(shape, True)):
+        assert (p["kernel"], p["tile_c"], p["tile_p"]) == (2, tile_c, 128)
+
+
 @pytest.mark.parametrize("shape", [(16, 14, 14, 64, 160, 1, 1, 0), (128, 14, 14, 192, 160, 1, 1, 0), (16, 14, 14, 128, 480, 1, 1, 0), (128, 14, 14, 64, 320, 1, 1, 0)])
 def test_short_contractions_into_multiples_of_160_go_direct_to_lds(shape):
     p = dat.conv_plan(shape)
